@@ -206,21 +206,31 @@ __device__ __forceinline__ void lds_column(const typename S::word* site, int v, 
 // piece with the value it already holds.  Predicated loads would be sunk by
 // the compiler into their store's branch and waited for one at a time.
 template <int K>
-__device__ __forceinline__ void copy_pieces(void* __restrict__ dst, const void* __restrict__ src, int pieces,
-                                            int tid, int nth) {
+__device__ __forceinline__ void pieces_issue(u32x4 (&r)[K], const void* __restrict__ src, int pieces, int tid, int nth) {
   const u32x4* s = static_cast<const u32x4*>(src);
-  u32x4* d = static_cast<u32x4*>(dst);
-  u32x4 r[K];
 #pragma unroll
   for (int j = 0; j < K; ++j) {
     const int i = tid + j * nth;
     r[j] = s[i < pieces ? i : pieces - 1];
   }
+}
+
+template <int K>
+__device__ __forceinline__ void pieces_commit(const u32x4 (&r)[K], void* __restrict__ dst, int pieces, int tid, int nth) {
+  u32x4* d = static_cast<u32x4*>(dst);
 #pragma unroll
   for (int j = 0; j < K; ++j) {
     const int i = tid + j * nth;
     d[i < pieces ? i : pieces - 1] = r[j];
   }
+}
+
+template <int K>
+__device__ __forceinline__ void copy_pieces(void* __restrict__ dst, const void* __restrict__ src, int pieces,
+                                            int tid, int nth) {
+  u32x4 r[K];
+  pieces_issue<K>(r, src, pieces, tid, nth);
+  pieces_commit<K>(r, dst, pieces, tid, nth);
 }
 
 // ---------------------------------------------------------------- output epilogues

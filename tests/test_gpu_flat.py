@@ -1,0 +1,78 @@
+"""D_W where a workgroup's sites run across the ends of x-rows: the row-staged
+kernels on lattices whose rows hold no chunk of their own, at every N_v they take,
+at the edges of their chunks (planes smaller than a chunk, a last chunk of one site,
+N_x = 2) against the FP64 oracle, with the
+tolerances of the other operator tests."""
+import pytest
+
+import synthetic
+from oracle import evenodd, wilson
+from tests.gpu_util import compare, down, rounded, say, set_knob, up
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+if not torch.cuda.is_available():
+    pytest.skip("no GPU", allow_module_level=True)
+
+from paper_1808_05506_amd import dslash as D  # noqa: E402
+
+
+def _fields(dims, nv, dt, seed):
+    u = rounded(synthetic.gauge_links(dims, "haar", seed), dt)
+    p = rounded(synthetic.wilson_spinor(dims, nv, seed + 1), dt)
+    return u, p
+
+
+# odd extents, rows shorter and longer than a chunk, a plane that is no multiple of
+# a chunk, N_x = 2 and 3 (both x neighbours are wraps), a plane of 4 sites, several
+# t segments and a last segment of one step
+SHAPES = [(7, 5, 3, 4), (13, 6, 2, 5), (37, 3, 2, 3), (2, 9, 3, 4), (3, 11, 2, 9), (2, 2, 3, 17)]
+
+
+@pytest.mark.parametrize("nv", [2, 3, 4, 5, 7, 10, 12, 13, 17, 19, 22, 23, 24])
+@pytest.mark.parametrize("dims", SHAPES)
+def test_wilson_chunks_across_rows(dims, nv):
+    say(f"case wilson chunks across rows {dims} nv={nv} c64")
+    u, p = _fields(dims, nv, "c64", 700 + nv)
+    U, P = up(u, "c64"), up(p, "c64")
+    for adj in (False, True):
+        compare(down(D.apply("wilson", U, P, 0.1, adjoint=adj)), wilson.apply(u, p, 0.1, adj), "c64",
+                f"D_W nv={nv} adj={adj}")
+
+
+@pytest.mark.parametrize("dt", ["bf16", "f16"])
+@pytest.mark.parametrize("nv", [4, 5, 8, 10, 12, 16, 24])
+@pytest.mark.parametrize("dims", SHAPES[:4])
+def test_wilson_16bit_chunks_across_rows(dims, nv, dt):
+    say(f"case wilson chunks across rows {dims} nv={nv} {dt}")
+    u, p = _fields(dims, nv, dt, 720 + nv)
+    out = D.apply("wilson", up(u, dt), up(p, dt), 0.1)
+    compare(down(out), wilson.apply(u, p, 0.1, False), dt, f"D_W nv={nv} {dt}")
+
+
+@pytest.mark.parametrize("dt", ["c64", "bf16"])
+@pytest.mark.parametrize("sites", ["9", "16", "21"])
+def test_wilson_chunk_lengths(sites, dt, monkeypatch):
+    dims, nv = (14, 5, 2, 9), 12
+    say(f"case wilson chunk length {sites} {dt}")
+    set_knob(monkeypatch, "DSLASH_ROW_SITES", sites)
+    u, p = _fields(dims, nv, dt, 740)
+    U, P = up(u, dt), up(p, dt)
+    for adj in (False, True):
+        compare(down(D.apply("wilson", U, P, 0.1, adjoint=adj)), wilson.apply(u, p, 0.1, adj), dt,
+                f"D_W R={sites} adj={adj}")
+
+
+# packed rows of 5, 7, 2 and 1 sites
+@pytest.mark.parametrize("dims", [(10, 4, 2, 4), (14, 6, 4, 2), (4, 8, 2, 6), (2, 4, 8, 2)])
+@pytest.mark.parametrize("dt,nv", [("c64", 12), ("c64", 4), ("bf16", 12), ("f16", 24), ("f16", 16), ("bf16", 8)])
+def test_even_odd_hop_chunks_across_rows(dims, dt, nv):
+    say(f"case even-odd chunks across rows {dims} nv={nv} {dt}")
+    u, p = _fields(dims, nv, dt, 820 + nv)
+    ue, uo = up(evenodd.pack(u, 0), dt), up(evenodd.pack(u, 1), dt)
+    for parity in (0, 1):
+        pin = evenodd.pack(p, 1 - parity)
+        for adj in (False, True):
+            compare(down(D.eo_hop(ue, uo, up(pin, dt), parity, adjoint=adj)), evenodd.hop_eo(u, pin, parity, adj), dt,
+                    f"eo hop parity={parity} adj={adj}")
