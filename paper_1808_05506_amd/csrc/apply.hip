@@ -177,6 +177,8 @@ hipError_t launch_apply(int op, bool adj, int dtype, const Geom& g, const void* 
       if (clover && compressed) return hipErrorInvalidValue;
       const hipError_t e = launch_wilson_rows(adj, dtype, g, U, in, out, mass, st, clover, compressed);
       if (e != hipErrorNotSupported || rows_only) return e;
+      const hipError_t f = launch_wilson_flat(adj, dtype, g, U, in, out, mass, st, clover, compressed);
+      if (f != hipErrorNotSupported) return f;
       return apply_op<OP_WILSON>(adj, dtype, g, U, in, out, clover, mass, compressed, st);
     }
     case OP_BRILLOUIN: {

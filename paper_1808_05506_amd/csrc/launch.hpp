@@ -24,7 +24,7 @@ struct Knob {
 struct Knobs {
   Knob sites_per_block, tband, xcd, row_sites, row_depth, tsteps, march_pp, rows, row_lds_extra, cg_fuse;
   Knob grad_tile_y, grad_tile_z, march_tile_y, march_tile_z, bri_tile_y, bri_tile_z, rows_tile_y,
-      rows_tile_z, blas_nt, wmarch_tile_y, wmarch_tile_z;
+      rows_tile_z, blas_nt, wmarch_tile_y, wmarch_tile_z, flat_zb, flat_kb;
 };
 inline Knob read_knob(const char* name) {
   Knob k;
@@ -57,6 +57,8 @@ inline Knobs read_knobs() {
   r.blas_nt = read_knob("DSLASH_BLAS_NT");
   r.wmarch_tile_y = read_knob("DSLASH_WMARCH_TILE_Y");
   r.wmarch_tile_z = read_knob("DSLASH_WMARCH_TILE_Z");
+  r.flat_zb = read_knob("DSLASH_FLAT_ZB");
+  r.flat_kb = read_knob("DSLASH_FLAT_KB");
   return r;
 }
 inline Knobs& knob_store() {
@@ -95,6 +97,12 @@ hipError_t launch_apply(int op, bool adjoint, int dtype, const Geom& g, const vo
 hipError_t launch_wilson_rows(bool adjoint, int dtype, const Geom& g, const void* U, const void* in, void* out,
                               double mass, hipStream_t st, const void* clover = nullptr, bool compressed = false,
                               int epi = 0, EpiArgs* ea = nullptr);
+// D_W at any N_v, storage and alignment by the flat kernel (wilson_flat.hpp);
+// hipErrorNotSupported where a plane of sites reaches 4 GB, or for an epilogue
+// that does not fit.
+hipError_t launch_wilson_flat(bool adjoint, int dtype, const Geom& g, const void* U, const void* in, void* out,
+                              double mass, hipStream_t st, const void* clover, bool compressed, int epi = 0,
+                              EpiArgs* ea = nullptr);
 hipError_t launch_staggered_rows(bool adjoint, int dtype, const Geom& g, const void* U, const void* in, void* out,
                                  double mass, hipStream_t st, bool compressed = false);
 hipError_t launch_compress_links(int dtype, size_t links, const void* V, void* Vc, hipStream_t st);

@@ -1,0 +1,76 @@
+// Flat D_W kernels on the full lattice (see wilson_flat.hpp): the launch shape
+// and the C64 and C128 forms.
+#include "wilson_flat.hpp"
+
+namespace dsl {
+
+// P: at most 256 lanes and 80 KB of links (two workgroups a CU), and of those
+// the one that wastes the fewest lanes on the chunk count and the last wave.
+// zb x kb: whole planes whose spinors at one t take at most 1.2 MB where two fit,
+// else three planes of about a third of 1.05 MB each.  FP64 takes two workgroups
+// a CU (79 KB of LDS asked for): more of them in flight than that push each
+// other's neighbour rows out of the L2.  FP64, N_v = 12, 24^3 x 48: 1141 us with
+// 3 planes x 7 of 28 chunks at two workgroups a CU, 1167 at three, 1368 with four
+// and the tile of the smallest surface; 16^3 x 32: 220 us with 2 whole planes, 230
+// with 4 planes x 7 of 13 chunks, 242 and 272 as before.
+FlatShape flat_shape(const Geom& g, int word_bytes, int vw, int lw, bool clover) {
+  FlatShape s{};
+  const uint32_t plane = uint32_t(g.n[0]) * uint32_t(g.n[1]);
+  const uint32_t groups = uint32_t(g.nv / vw), gb = groups < 256 ? groups : 256;
+  const size_t site_lds = size_t(8 * lw + (clover ? 36 : 0)) * word_bytes;
+  uint32_t pmax = 256 / gb;
+  if (pmax > 80 * 1024 / site_lds) pmax = uint32_t(80 * 1024 / site_lds);
+  if (pmax > plane) pmax = plane;
+  if (pmax < 1) pmax = 1;
+  uint32_t best = pmax;
+  double cost = 0;
+  for (uint32_t p = pmax; p >= 1 && 2 * p >= pmax; --p) {
+    const double lanes = double((plane + p - 1) / p) * ((p * gb + 63) / 64) * 64;
+    if (cost == 0 || lanes < 0.9 * cost) {
+      cost = lanes;
+      best = p;
+    }
+  }
+  s.o.P = best;
+  s.o.chunks = (plane + best - 1) / best;
+  s.o.groups = FastDiv::make(gb);
+  const double row = 12.0 * g.nv * word_bytes * best, full = row * s.o.chunks;
+  if (full <= 0.6 * 1024 * 1024) {
+    s.o.kb = s.o.chunks;
+    s.o.zb = uint32_t(1.2 * 1024 * 1024 / full);
+    if (s.o.zb > uint32_t(g.n[2])) s.o.zb = uint32_t(g.n[2]);
+  } else {
+    s.o.zb = g.n[2] < 3 ? uint32_t(g.n[2]) : 3u;
+    s.o.kb = uint32_t(1.05 * 1024 * 1024 / (s.o.zb * row));
+    if (s.o.kb < 1) s.o.kb = 1;
+    if (s.o.kb > s.o.chunks) s.o.kb = s.o.chunks;
+  }
+  if (knobs().flat_zb.set) s.o.zb = uint32_t(knobs().flat_zb.value);
+  if (knobs().flat_kb.set) s.o.kb = uint32_t(knobs().flat_kb.value);
+  s.grid = dim3(s.o.chunks * uint32_t(g.n[2]) * uint32_t(g.n[3]), (groups + gb - 1) / gb);
+  s.block = dim3(best * gb);
+  s.lds = size_t(best) * site_lds;
+  if (word_bytes == 16 && s.lds < 79 * 1024) s.lds = 79 * 1024;
+  if (s.lds < size_t(knobs().row_lds_extra.get(0))) s.lds = size_t(knobs().row_lds_extra.get(0));
+  return s;
+}
+
+// Left to the direct kernel, which is faster there: N_v = 1 (16^3 x 32 C64 26.6
+// against 66.4 us, its site is one contiguous run), and lanes of one 8- or 4-byte
+// word where the links are short or few lanes share them (C64 compressed, N_v = 5,
+// 22 x 20 x 13 x 21: 71.5 against 93 us; BF16, N_v = 5, 20 x 18 x 14 x 22: 59.9
+// against 68; FP16, N_v = 7: 88.9 against 81.8, so from N_v = 6 on this one).
+hipError_t launch_wilson_flat(bool adj, int dtype, const Geom& g, const void* U, const void* in, void* out, double mass,
+                              hipStream_t st, const void* clover, bool compressed, int epi, EpiArgs* ea) {
+  if (!flat_covers(g, dtype)) return hipErrorNotSupported;
+  const bool one_word = dtype != DT_C128 && flat_vw(dtype, g.nv, aligned16(in) && aligned16(out)) == 1;
+  if (!clover && epi == EPI_STORE && (g.nv == 1 || (one_word && (compressed || g.nv < 6)))) return hipErrorNotSupported;
+  EpiArgs none;
+  EpiArgs& e = ea ? *ea : none;
+  const int vw = flat_vw(dtype, g.nv, aligned16(in) && aligned16(out));
+  const FlatArgs a{U, U, in, in, clover, out, 4.0 + mass, -0.5, 0};
+  if (dtype == DT_BF16 || dtype == DT_F16) return launch_wilson_flat16(dtype, vw, adj, g, a, compressed, epi, st, e);
+  return flat_forms_wide<false>(dtype, vw, adj, g, a, compressed, epi, st, e);
+}
+
+}  // namespace dsl

@@ -1,12 +1,13 @@
 """D_W where a workgroup's sites run across the ends of x-rows: the row-staged
 kernels on lattices whose rows hold no chunk of their own, at every N_v they take,
-at the edges of their chunks (planes smaller than a chunk, a last chunk of one site,
-N_x = 2) against the FP64 oracle, with the
+and the direct kernel for FP64, the clover term, compressed links and 16-bit
+storage, at the edges of their chunks (planes smaller than a chunk, a last chunk of
+one site, N_x = 2, columns past one workgroup) against the FP64 oracle, with the
 tolerances of the other operator tests."""
 import pytest
 
 import synthetic
-from oracle import evenodd, wilson
+from oracle import clover, compress, evenodd, wilson
 from tests.gpu_util import compare, down, rounded, say, set_knob, up
 
 pytestmark = pytest.mark.gpu
@@ -62,6 +63,57 @@ def test_wilson_chunk_lengths(sites, dt, monkeypatch):
     for adj in (False, True):
         compare(down(D.apply("wilson", U, P, 0.1, adjoint=adj)), wilson.apply(u, p, 0.1, adj), dt,
                 f"D_W R={sites} adj={adj}")
+
+
+@pytest.mark.parametrize("nv", [1, 2, 6, 7, 12, 25, 130, 260])
+@pytest.mark.parametrize("dims", [(5, 3, 2, 4), (2, 7, 3, 3), (10, 4, 5, 2)])
+def test_wilson_fp64_flat(dims, nv):
+    say(f"case wilson flat {dims} nv={nv} c128")
+    u, p = _fields(dims, nv, "c128", 760 + nv)
+    U, P = up(u, "c128"), up(p, "c128")
+    for adj in (False, True):
+        compare(down(D.apply("wilson", U, P, 0.1, adjoint=adj)), wilson.apply(u, p, 0.1, adj), "c128",
+                f"D_W nv={nv} adj={adj}")
+
+
+@pytest.mark.parametrize("dt,nv", [("c128", 7), ("c64", 5), ("c64", 26), ("f16", 9), ("bf16", 12)])
+@pytest.mark.parametrize("dims", [(5, 3, 2, 4), (10, 4, 5, 2)])
+def test_wilson_flat_clover_and_compressed(dims, dt, nv):
+    say(f"case wilson flat clover and compressed {dims} nv={nv} {dt}")
+    u, p = _fields(dims, nv, dt, 780 + nv)
+    c = rounded(clover.pack(clover.term(u, 1.3)), dt)
+    vc = rounded(compress.compress(synthetic.gauge_links(dims, "smooth", 780)), dt)
+    U, P, C, VC = up(u, dt), up(p, dt), up(c, dt), up(vc, dt)
+    for adj in (False, True):
+        compare(down(D.apply("wilson", U, P, 0.1, adjoint=adj, clover=C)),
+                wilson.apply(u, p, 0.1, adj) + clover.apply_term(clover.unpack(c), p), dt, f"clover adj={adj}")
+        compare(down(D.apply_compressed("wilson", VC, P, 0.1, adjoint=adj)),
+                compress.apply("wilson", vc, p, 0.1, adj), dt, f"compressed adj={adj}")
+
+
+@pytest.mark.parametrize("tile", [("1", "1"), ("2", "2"), ("5", "3"), ("100", "100")])
+def test_wilson_flat_tiles(tile, monkeypatch):
+    # every order visits every chunk once, also tiles that divide nothing
+    dims, nv = (9, 30, 5, 3), 12
+    say(f"case wilson flat tile {tile}")
+    set_knob(monkeypatch, "DSLASH_FLAT_ZB", tile[0])
+    set_knob(monkeypatch, "DSLASH_FLAT_KB", tile[1])
+    u, p = _fields(dims, nv, "c128", 790)
+    compare(down(D.apply("wilson", up(u, "c128"), up(p, "c128"), 0.1)), wilson.apply(u, p, 0.1, False), "c128",
+            f"tile {tile}")
+
+
+@pytest.mark.parametrize("dt", ["c64", "c128"])
+def test_wilson_misaligned_pointers_take_narrow_words(dt):
+    # spinors that begin one complex number past a 16-byte border
+    dims, nv = (6, 5, 3, 4), 12
+    say(f"case wilson misaligned {dt}")
+    u, p = _fields(dims, nv, dt, 800)
+    U, P = up(u, dt), up(p, dt)
+    hold = torch.zeros(P.numel() + 1, dtype=P.dtype, device=P.device)
+    Q = hold[1:].view(P.shape)
+    Q.copy_(P)
+    compare(down(D.apply("wilson", U, Q, 0.1)), wilson.apply(u, p, 0.1, False), dt, f"misaligned {dt}")
 
 
 # packed rows of 5, 7, 2 and 1 sites
