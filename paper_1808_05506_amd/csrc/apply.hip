@@ -183,7 +183,7 @@ hipError_t launch_apply(int op, bool adj, int dtype, const Geom& g, const void* 
     }
     case OP_BRILLOUIN: {
       if (compressed) return hipErrorInvalidValue;
-      const hipError_t e = launch_brillouin_rows(adj, dtype, g, U, in, out, mass, st, clover);
+      const hipError_t e = launch_brillouin_flat(adj, dtype, g, U, in, out, mass, st, clover);
       if (e != hipErrorNotSupported || rows_only) return e;
       return apply_op<OP_BRILLOUIN>(adj, dtype, g, U, in, out, clover, mass, false, st);
     }

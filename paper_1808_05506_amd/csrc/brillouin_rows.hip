@@ -1,12 +1,11 @@
-// Row-staged D_B (Sec. 5; see rows.hpp for the row staging).  A workgroup
+// Row-staged D_B with its off-axis links built on the fly (Sec. 5; see rows.hpp for
+// the row staging), and the gradient with respect to W.  A workgroup
 // owns an x-row chunk of R sites and all N_v right-hand sides (thread (x, v)).
 // The 80 hops of the 3^4 stencil reach the 27 rows (y + dy, z + dz, t + dt),
 // dy, dz, dt in {-1, 0, 1}; each such row is staged once, with the halo sites
 // x0 - 1 and x0 + n, through one LDS buffer with coalesced 16-byte loads, and
-// serves the hops d = (dx, dy, dz, dt), dx in {-1, 0, 1}.  With each row come
-// the three link columns those hops need: W_d(x) at the chunk's own sites when
-// d is one of the 40 stored directions, else W_{-d}(x + d) at the neighbour
-// row's sites, applied as its adjoint.  Thread (x, v) accumulates
+// serves the hops d = (dx, dy, dz, dt), dx in {-1, 0, 1}; the three link columns
+// W_d(x) of those hops are built from V in LDS.  Thread (x, v) accumulates
 //   out(x) = (m0 + 15/8) psi(x) + sum_d (-lambda_k / 2 + rho_k d.gamma) W_d(x) psi(x + d)
 // (rho_k -> -rho_k for the adjoint) in registers over the 27 rows and writes
 // its output once, through LDS with coalesced 16-byte stores.
@@ -45,7 +44,6 @@ struct BriStage {
   static constexpr int SW = 12 * NV;                  // words per site
   static constexpr int SP = SW * int(sizeof(W)) / 16; // 16-byte pieces per site
   static constexpr int CH = SP / NV;                  // pieces per lane
-  static constexpr int KW = (27 + NV - 1) / NV;       // link words per thread (27 n words per row)
   // halo pieces per thread (2 SP = 12 N_v of them over R N_v threads): one
   // for chunks of at least 12 sites, two for the chunks of 6 .. 11 sites
   // taken at N_v > 16 (the launcher checks R HK >= 12)
@@ -58,13 +56,11 @@ template <int NV, class S>
 struct BriRowRegs {
   u32x4 p[BriStage<NV, S>::CH];
   u32x4 halo[BriStage<NV, S>::HK];
-  typename S::word w[BriStage<NV, S>::KW];
 };
 
-template <bool FLY, int NV, class S>
-__device__ __forceinline__ void bri_issue(const Geom& g, const RowChunk& c, const typename S::word* __restrict__ Wl,
-                                          const typename S::word* __restrict__ in, int r, int xm, int xp, int xl,
-                                          int v, int tid, int nth, BriRowRegs<NV, S>& q) {
+template <int NV, class S>
+__device__ __forceinline__ void bri_issue(const Geom& g, const RowChunk& c, const typename S::word* __restrict__ in, int r,
+                                          int xm, int xp, int xl, int v, int tid, int nth, BriRowRegs<NV, S>& q) {
   using St = BriStage<NV, S>;
   int dy, dz, dt;
   bri_row_offset(r, dy, dz, dt);
@@ -80,33 +76,11 @@ __device__ __forceinline__ void bri_issue(const Geom& g, const RowChunk& c, cons
     const int hs = h < St::SP ? xm : xp;
     q.halo[k] = reinterpret_cast<const u32x4*>(in + size_t(nb + hs) * St::SW)[h < St::SP ? h : h - St::SP];
   }
-  // link columns dx = -1, 0, 1: 9 words per site of the chunk (built from V
-  // in LDS instead when FLY)
-  if constexpr (FLY) return;
-  const int nw = 27 * c.n;
-#pragma unroll
-  for (int k = 0; k < St::KW; ++k) {
-    int w = tid + k * nth;
-    w = w < nw ? w : nw - 1;
-    const int col = w / (9 * c.n), rem = w - col * 9 * c.n;
-    const int site = rem / 9, e = rem - site * 9;
-    const int dx = col - 1;
-    const int code = bri_code(dx, dy, dz, dt);
-    size_t idx;
-    if (code > 40) {
-      idx = (size_t(c.row_base + c.x0 + site) * 40 + (code - 41)) * 9 + e;  // W_d(x), stored
-    } else {
-      // W_{-d}(x + d), slot n(-d) - 41 = 39 - n(d); for d = 0 any valid word (unused)
-      const int slot = code == 40 ? 0 : 39 - code;
-      idx = (size_t(nb + wrap_x(g, c.x0 + site + dx)) * 40 + slot) * 9 + e;
-    }
-    q.w[k] = Wl[idx];
-  }
 }
 
-template <bool FLY, int NV, class S>
+template <int NV, class S>
 __device__ __forceinline__ void bri_commit(const RowChunk& c, const BriRowRegs<NV, S>& q, typename S::word* buf,
-                                           typename S::word* wbuf, int R, int xl, int v, int tid, int nth) {
+                                           int xl, int v, int tid, int nth) {
   using St = BriStage<NV, S>;
   constexpr int SSP = SiteStride<NV, S>::PIECES;
   const int xc = xl < c.n ? xl : c.n - 1;
@@ -120,37 +94,23 @@ __device__ __forceinline__ void bri_commit(const RowChunk& c, const BriRowRegs<N
     u32x4* hdst = reinterpret_cast<u32x4*>(buf) + (h < St::SP ? 0 : (c.n + 1) * SSP);
     hdst[h < St::SP ? h : h - St::SP] = q.halo[k];
   }
-  if constexpr (FLY) return;
-  const int nw = 27 * c.n;
-#pragma unroll
-  for (int k = 0; k < St::KW; ++k) {
-    int w = tid + k * nth;
-    w = w < nw ? w : nw - 1;
-    const int col = w / (9 * c.n), rem = w - col * 9 * c.n;
-    wbuf[col * R * 9 + rem] = q.w[k];
-  }
 }
 
-// acc += (a + b d.gamma) chi for chi = W' psi, one hop of row (dy, dz, dt)
+// acc += (a + b d.gamma) chi for chi = W psi, one hop of row (dy, dz, dt)
 template <int NV, class S, class T>
-__device__ __forceinline__ void bri_hop(const typename S::word* site, const typename S::word* link, bool dag, int v,
-                                        T a, T B1, T B2, T B3, T B4, int d0, int d1, int d2, int d3,
+__device__ __forceinline__ void bri_hop(const typename S::word* site, const typename S::word* link, int v, T a,
+                                        T B1, T B2, T B3, T B4, int d0, int d1, int d2, int d3,
                                         cpx<T> (&acc)[4][3]) {
   cpx<T> u[3][3], p[4][3];
-  // W' = link or its adjoint (dag is the same for every lane)
 #pragma unroll
   for (int i = 0; i < 3; ++i)
 #pragma unroll
-    for (int j = 0; j < 3; ++j) {
-      const cpx<T> l = S::template load<T>(link + (dag ? j * 3 + i : i * 3 + j));
-      u[i][j].r = l.r;
-      u[i][j].i = dag ? -l.i : l.i;
-    }
+    for (int j = 0; j < 3; ++j) u[i][j] = S::template load<T>(link + i * 3 + j);
 #pragma unroll
   for (int sp = 0; sp < 4; ++sp)
 #pragma unroll
     for (int cc = 0; cc < 3; ++cc) p[sp][cc] = S::template load<T>(site + (sp * 3 + cc) * NV + v);
-  // one colour row of chi = W' psi at a time (the spin factor does not mix
+  // one colour row of chi = W psi at a time (the spin factor does not mix
   // colours): upper spins += S chi_low, lower += S^dag chi_up with
   // S = sum_mu d_mu s_mu; d_mu is the same for every lane (uniform branches)
 #pragma unroll
@@ -239,9 +199,8 @@ __device__ __forceinline__ void bri_build(const Geom& g, const RowChunk& c, cons
 }
 
 // The three hops of staged row r (and the diagonal term, with the clover term
-// if CLOV, for the own row).  FLY: the link columns hold W_d(x) for all three
-// hops (built in place), never an adjoint.
-template <bool ADJ, bool CLOV, bool FLY, int NV, class S, class T>
+// if CLOV, for the own row).
+template <bool ADJ, bool CLOV, int NV, class S, class T>
 __device__ __forceinline__ void bri_row_compute(int r, const typename S::word* buf, const typename S::word* wbuf,
                                                 const typename S::word* lcl, int R, int xl, int v, T diag,
                                                 cpx<T> (&acc)[4][3]) {
@@ -276,7 +235,7 @@ __device__ __forceinline__ void bri_row_compute(int r, const typename S::word* b
     const T a = T(-0.5) * bri_lambda<T>(k);
     const T b = (ADJ ? T(-1) : T(1)) * bri_rho<T>(k);
     const typename S::word* link = wbuf + (dx + 1) * R * 9 + xl * 9;
-    bri_hop<NV, S, T>(site, link, !FLY && bri_code(dx, dy, dz, dt) <= 40, v, a, b * T(dx), b * T(dy), b * T(dz),
+    bri_hop<NV, S, T>(site, link, v, a, b * T(dx), b * T(dy), b * T(dz),
                       b * T(dt), dx, dy, dz, dt, acc);
   }
 }
@@ -284,16 +243,14 @@ __device__ __forceinline__ void bri_row_compute(int r, const typename S::word* b
 
 }  // namespace
 
-// Waves per SIMD: three (168 VGPRs); two below N_v = 8, where a thread moves
-// ceil(27 / N_v) link words of every staged row.
+// Waves per SIMD: three (168 VGPRs); two below N_v = 8.
 template <int NV> struct BriWaves { static constexpr int value = NV < 8 ? 2 : 3; };
 
 // CLOV: adds the site-local clover term (packed, 36 words per site, staged
-// in LDS after the link columns).  FLY: Wl holds the one-hop links V and the
-// off-axis links are built on the fly for every row.
-template <bool ADJ, bool CLOV, bool FLY, int NV, class S, class T>
+// in LDS after the link columns).
+template <bool ADJ, bool CLOV, int NV, class S, class T>
 __global__ void __launch_bounds__(256, BriWaves<NV>::value)
-    brillouin_rows_kernel(Geom g, RowTraversal tr, ChunkTiles o, int xcd, const typename S::word* __restrict__ Wl,
+    brillouin_rows_kernel(Geom g, RowTraversal tr, ChunkTiles o, int xcd, const typename S::word* __restrict__ V,
                           const typename S::word* __restrict__ in, typename S::word* __restrict__ out,
                           const typename S::word* __restrict__ C, T diag) {
   using W = typename S::word;
@@ -324,14 +281,14 @@ __global__ void __launch_bounds__(256, BriWaves<NV>::value)
   constexpr int CLP = 36 * int(sizeof(W)) / 16;  // 16-byte pieces of a site's clover term
   if constexpr (CLOV) copy_pieces<(CLP + NV - 1) / NV>(lcl, C + size_t(c.row_base + c.x0) * 36, c.n * CLP, tid, nth);
   BriRowRegs<NV, S> q;
-  bri_issue<FLY, NV, S>(g, c, Wl, in, 0, xm, xp, xl, v, tid, nth, q);
+  bri_issue<NV, S>(g, c, in, 0, xm, xp, xl, v, tid, nth, q);
 #pragma nounroll
   for (int r = 0; r < kBriRows; ++r) {
-    bri_commit<FLY, NV, S>(c, q, buf, wbuf, R, xl, v, tid, nth);
-    if constexpr (FLY) bri_build<S, T>(g, c, Wl, r, wbuf, R, tid, nth);
+    bri_commit<NV, S>(c, q, buf, xl, v, tid, nth);
+    bri_build<S, T>(g, c, V, r, wbuf, R, tid, nth);
     __syncthreads();
-    bri_issue<FLY, NV, S>(g, c, Wl, in, r + 1 < kBriRows ? r + 1 : kBriRows - 1, xm, xp, xl, v, tid, nth, q);
-    bri_row_compute<ADJ, CLOV, FLY, NV, S, T>(r, buf, wbuf, lcl, R, xl, v, diag, acc);
+    bri_issue<NV, S>(g, c, in, r + 1 < kBriRows ? r + 1 : kBriRows - 1, xm, xp, xl, v, tid, nth, q);
+    bri_row_compute<ADJ, CLOV, NV, S, T>(r, buf, wbuf, lcl, R, xl, v, diag, acc);
     __syncthreads();
   }
   // output through LDS, coalesced 16-byte stores
@@ -359,10 +316,8 @@ __global__ void __launch_bounds__(256, BriWaves<NV>::value)
 // bz | Nz) whose spinor rows at one t take at most 1.25 MB, the squarer of
 // equal sizes, by >= bz on a tie; DSLASH_BRI_TILE_Y, _Z override (0: t-band
 // order).  Each output row stages the 27 rows around it, and in the t-band
-// order its +-z rows were a band of planes away, gone from the XCD's L2.  On
-// 32^4, N_v = 12: FP64 4 x 4, 16.72 against 17.77 ms (2 x 2: 18.00, 8 x 8:
-// 17.03); FP32 8 x 4, 7.09 against 7.39 ms (4 x 4: 7.18, 8 x 8: 7.21); W on
-// the fly 23.8 against 24.5 ms.  The W-gradient kernel gained nothing (6.96
+// order its +-z rows were a band of planes away, gone from the XCD's L2: 32^4,
+// N_v = 12, 23.8 against 24.5 ms.  The W-gradient kernel gained nothing (6.96
 // ms either way) and keeps the t-band order (tiled = false).
 static ChunkTiles bri_tiles(const Geom& g, int R, long site_bytes, bool tiled = true) {
   int by, bz;
@@ -371,8 +326,8 @@ static ChunkTiles bri_tiles(const Geom& g, int R, long site_bytes, bool tiled = 
 }
 
 // CLOVER_OK = false builds the form without the clover term only (C must be null).
-template <int NV, class S, class T, bool FLY, bool CLOVER_OK = true>
-static hipError_t brillouin_rows_t(bool adj, const Geom& g, int R, int bt, bool xcd, const void* Wl, const void* in,
+template <int NV, class S, class T, bool CLOVER_OK = true>
+static hipError_t brillouin_rows_t(bool adj, const Geom& g, int R, int bt, bool xcd, const void* V, const void* in,
                                    void* out, const void* C, double mass, hipStream_t st) {
   using W = typename S::word;
   const RowTraversal tr = make_row_traversal(g, uint32_t(R), uint32_t(bt));
@@ -382,7 +337,7 @@ static hipError_t brillouin_rows_t(bool adj, const Geom& g, int R, int bt, bool 
       (size_t(R + 2) * SiteStride<NV, S>::WORDS + size_t(3 * R) * 9 + (C ? 3 + size_t(R) * 36 : 0)) * sizeof(W);
   const T diag = T(mass) + T(15.0 / 8.0);
 #define DSL_BK(A, CL)                                                                                        \
-  hipLaunchKernelGGL((brillouin_rows_kernel<A, CL, FLY, NV, S, T>), grid, block, lds, st, g, tr, o, int(xcd), (const W*)Wl, \
+  hipLaunchKernelGGL((brillouin_rows_kernel<A, CL, NV, S, T>), grid, block, lds, st, g, tr, o, int(xcd), (const W*)V, \
                      (const W*)in, (W*)out, (const W*)C, diag)
   if constexpr (CLOVER_OK) {
     if (C) {
@@ -507,7 +462,7 @@ __global__ void __launch_bounds__(256, 3)
       }
   }
   BriRowRegs<NV, S> qr;
-  bri_issue<true, NV, S>(g, c, nullptr, psi, kWgFirstRow, xm, xp, xl, v, tid, nth, qr);
+  bri_issue<NV, S>(g, c, psi, kWgFirstRow, xm, xp, xl, v, tid, nth, qr);
 #pragma nounroll
   for (int r = kWgFirstRow; r < kBriRows; ++r) {
     int dy, dz, dt;
@@ -516,10 +471,10 @@ __global__ void __launch_bounds__(256, 3)
     for (int phase = 0; phase < 2; ++phase) {
       // phase 0 stages psi of the row, phase 1 chi; each requests the next run
       __syncthreads();  // the staged run and the sums of the previous phase or row are read
-      bri_commit<true, NV, S>(c, qr, bs, nullptr, R, xl, v, tid, nth);
+      bri_commit<NV, S>(c, qr, bs, xl, v, tid, nth);
       __syncthreads();
       const int rn = phase == 0 ? r : (r + 1 < kBriRows ? r + 1 : kBriRows - 1);
-      bri_issue<true, NV, S>(g, c, nullptr, phase == 0 ? chi : psi, rn, xm, xp, xl, v, tid, nth, qr);
+      bri_issue<NV, S>(g, c, phase == 0 ? chi : psi, rn, xm, xp, xl, v, tid, nth, qr);
 #pragma unroll
       for (int dx = -1; dx <= 1; ++dx) {
         if (r == kWgFirstRow && dx != 1) continue;
@@ -583,199 +538,7 @@ static hipError_t brillouin_wgrad_rows_t(const Geom& g, int R, int bt, bool xcd,
   return hipGetLastError();
 }
 
-// ---------------------------------------------------------------- FP64, staged straight into LDS
-// The FP64 D_B keeps the row staging of brillouin_rows_kernel, but its rows
-// are copied from global memory into LDS by the direct-to-LDS load path
-// (global_load_lds_dwordx4: lane l of a wave writes LDS bytes [b + 16 l,
-// b + 16 l + 16) for a wave-uniform b), so no staged row passes through
-// registers.  With the hop computed one colour row of the link at a time the
-// kernel fits three waves per SIMD, where register staging of FP64 rows
-// allowed one.  A row in LDS is [halo x0 - 1][the chunk's n sites][halo
-// x0 + n] without padding (16-byte reads of consecutive lanes fall on
-// consecutive banks), then its three link columns [dx + 1][site][9].
-// Workgroup: 16 sites x N_v right-hand sides, a multiple of 64 threads, so
-// every wave covers whole 64-piece LDS ranges; chunks of fewer live sites
-// (the row's last, or rows shorter than 16) stage only their own.
-constexpr int kDmaSites = 16;
-
-__device__ __forceinline__ void lds_dma16(const void* src, void* lds_wave_base) {
-  __builtin_amdgcn_global_load_lds(src, (__attribute__((address_space(3))) void*)lds_wave_base, 16, 0, 0);
-}
-
-// Stage row r (spinor run with halos, three link columns) of chunk c into buf
-// and wbuf: LDS piece L of the row is loaded by lane L % 64 of wave
-// (L / 64) % waves, instruction L / (64 waves).
-template <int NV>
-__device__ __forceinline__ void bri_dma_row(const Geom& g, const RowChunk& c, const C128::word* __restrict__ Wl,
-                                            const C128::word* __restrict__ in, int r, int xm, int xp, int wave,
-                                            int lane, int waves, char* buf, char* wbuf) {
-  constexpr int SP = 12 * NV;  // 16-byte pieces (FP64 complex words) per site
-  int dy, dz, dt;
-  bri_row_offset(r, dy, dz, dt);
-  const uint32_t nb = bri_row_base(g, c, dy, dz, dt);
-  const int np = (c.n + 2) * SP;
-  for (int base = wave * 64; base < np; base += waves * 64) {
-    const int L = base + lane;
-    if (L < np) {
-      const int slot = L / SP, pp = L - slot * SP;
-      const int site = slot == 0 ? xm : (slot == c.n + 1 ? xp : c.x0 + slot - 1);
-      lds_dma16(in + size_t(nb + site) * SP + pp, buf + size_t(__builtin_amdgcn_readfirstlane(base)) * 16);
-    }
-  }
-  const int nw = 27 * kDmaSites;
-  for (int base = wave * 64; base < nw; base += waves * 64) {
-    const int L = base + lane;
-    if (L < nw) {
-      const int col = L / (9 * kDmaSites), rem = L - col * 9 * kDmaSites;
-      int site = rem / 9;
-      const int e = rem - site * 9;
-      site = site < c.n ? site : c.n - 1;
-      const int code = bri_code(col - 1, dy, dz, dt);
-      size_t idx;
-      if (code > 40) {
-        idx = (size_t(c.row_base + c.x0 + site) * 40 + (code - 41)) * 9 + e;  // W_d(x), stored
-      } else {
-        const int slot = code == 40 ? 0 : 39 - code;  // W_{-d}(x + d); d = 0: any valid word (unused)
-        idx = (size_t(nb + wrap_x(g, c.x0 + site + col - 1)) * 40 + slot) * 9 + e;
-      }
-      lds_dma16(Wl + idx, wbuf + size_t(__builtin_amdgcn_readfirstlane(base)) * 16);
-    }
-  }
-}
-
-// acc += (a + b d.gamma) W' psi for one hop, W' = the link or its adjoint,
-// taken one source spin at a time: chi_q = W' psi_q (one colour triple) goes
-// to acc_q with weight a and, for every non-zero d_mu, to the spin that
-// gamma_mu pairs with q (chiral basis, as in bri_hop), so only psi_q and chi_q
-// are live beside the link.
-template <int NV, class T>
-__device__ __forceinline__ void bri_hop_lean(const C128::word* site, const C128::word* link, bool dag, int v, T a,
-                                             T B1, T B2, T B3, T B4, int d0, int d1, int d2, int d3,
-                                             cpx<T> (&acc)[4][3]) {
-  cpx<T> u[3][3];
-#pragma unroll
-  for (int i = 0; i < 3; ++i)
-#pragma unroll
-    for (int j = 0; j < 3; ++j) {
-      const cpx<T> l = C128::template load<T>(link + (dag ? j * 3 + i : i * 3 + j));
-      u[i][j].r = l.r;
-      u[i][j].i = dag ? -l.i : l.i;
-    }
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    cpx<T> p[3], chi[3];
-#pragma unroll
-    for (int b = 0; b < 3; ++b) p[b] = C128::template load<T>(site + (q * 3 + b) * NV + v);
-#pragma unroll
-    for (int cc = 0; cc < 3; ++cc) {
-      cpx<T> t = zero<T>();
-#pragma unroll
-      for (int b = 0; b < 3; ++b) t = cmadd(t, u[cc][b], p[b]);
-      chi[cc] = t;
-      acc[q][cc] = rmadd(acc[q][cc], a, t);
-    }
-    // partner spins: gamma_4 and gamma_3 pair q with q ^ 2, gamma_2 and gamma_1
-    // with 3 - q; the factors, by source spin q = 0, 1, 2, 3:
-    //   gamma_4: B4 (all)   gamma_3: i B3 (+, -, -, +)
-    //   gamma_2: B2 (-, +, +, -)   gamma_1: i B1 (+, +, -, -)
-    const int P43 = q ^ 2, P21 = 3 - q;
-    const T s3 = (q == 1 || q == 2) ? T(-1) : T(1);
-    const T s2 = (q == 1 || q == 2) ? T(1) : T(-1);
-    const T s1 = q <= 1 ? T(1) : T(-1);
-    // d is uniform over the workgroup: scalar branches skip the zero axes
-    if (__builtin_amdgcn_readfirstlane(d3) != 0) {
-#pragma unroll
-      for (int cc = 0; cc < 3; ++cc) acc[P43][cc] = rmadd(acc[P43][cc], B4, chi[cc]);
-    }
-    if (__builtin_amdgcn_readfirstlane(d2) != 0) {
-#pragma unroll
-      for (int cc = 0; cc < 3; ++cc) acc[P43][cc] = cmadd_i(acc[P43][cc], s3 * B3, chi[cc]);
-    }
-    if (__builtin_amdgcn_readfirstlane(d1) != 0) {
-#pragma unroll
-      for (int cc = 0; cc < 3; ++cc) acc[P21][cc] = rmadd(acc[P21][cc], s2 * B2, chi[cc]);
-    }
-    if (__builtin_amdgcn_readfirstlane(d0) != 0) {
-#pragma unroll
-      for (int cc = 0; cc < 3; ++cc) acc[P21][cc] = cmadd_i(acc[P21][cc], s1 * B1, chi[cc]);
-    }
-  }
-#pragma unroll
-  for (int q = 0; q < 4; ++q)
-#pragma unroll
-    for (int cc = 0; cc < 3; ++cc) hold(acc[q][cc]);
-}
-
-constexpr size_t kDmaRowBytes = (size_t(kDmaSites + 2) * 12 * 12 + size_t(27) * kDmaSites) * 16;
-
-// One row buffer, three workgroups per CU: each loads a row, then applies it,
-// while the others do the same out of step.
-template <bool ADJ, int NV>
-__global__ void __launch_bounds__(kDmaSites * NV, 3)
-    brillouin_rows_dma_kernel(Geom g, RowTraversal tr, ChunkTiles o, int xcd, const C128::word* __restrict__ Wl,
-                              const C128::word* __restrict__ in, C128::word* __restrict__ out, double diag) {
-  using T = double;
-  constexpr int SW = 12 * NV;
-  extern __shared__ uint4 smem_bdma[];
-  char* const buf = reinterpret_cast<char*>(smem_bdma);       // [(16 + 2) SW] pieces: the row with its halos
-  char* const wbuf = buf + size_t(kDmaSites + 2) * SW * 16;   // [3][16][9] pieces: its link columns
-
-  const uint32_t L = xcd_block(blockIdx.x, gridDim.x, xcd != 0);
-  const RowChunk c = order_chunk(g, tr, o, L);
-  const int v = threadIdx.x, xl = threadIdx.y;
-  const int tid = xl * NV + v;
-  const int wave = tid >> 6, lane = tid & 63, waves = kDmaSites * NV / 64;
-  const int xm = wrap_x(g, c.x0 - 1), xp = wrap_x(g, c.x0 + c.n);
-
-  cpx<T> acc[4][3];
-#pragma unroll
-  for (int q = 0; q < 4; ++q)
-#pragma unroll
-    for (int cc = 0; cc < 3; ++cc) acc[q][cc] = zero<T>();
-
-#pragma nounroll
-  for (int r = 0; r < kBriRows; ++r) {
-    __syncthreads();  // the previous row's hops are done with the buffers
-    bri_dma_row<NV>(g, c, Wl, in, r, xm, xp, wave, lane, waves, buf, wbuf);
-    __builtin_amdgcn_s_waitcnt(0);
-    __syncthreads();
-    const C128::word* lrow = reinterpret_cast<const C128::word*>(buf);
-    const C128::word* lw = reinterpret_cast<const C128::word*>(wbuf);
-    int dy, dz, dt;
-    bri_row_offset(r, dy, dz, dt);
-#pragma unroll
-    for (int dx = -1; dx <= 1; ++dx) {
-      const int k = (dx != 0) + (dy != 0) + (dz != 0) + (dt != 0);
-      const C128::word* site = lrow + (xl + 1 + dx) * SW;
-      if (k == 0) {
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-#pragma unroll
-          for (int cc = 0; cc < 3; ++cc)
-            acc[q][cc] = rmadd(acc[q][cc], diag, C128::template load<T>(site + (q * 3 + cc) * NV + v));
-        continue;
-      }
-      const T a = T(-0.5) * bri_lambda<T>(k);
-      const T b = (ADJ ? T(-1) : T(1)) * bri_rho<T>(k);
-      const C128::word* link = lw + ((dx + 1) * kDmaSites + xl) * 9;
-      bri_hop_lean<NV, T>(site, link, bri_code(dx, dy, dz, dt) <= 40, v, a, b * T(dx), b * T(dy), b * T(dz),
-                          b * T(dt), dx, dy, dz, dt, acc);
-    }
-  }
-  // each lane writes its own 12 words: the N_v lanes of a site cover 16 N_v
-  // contiguous bytes per component
-  if (xl < c.n) {
-    u32x4* o = reinterpret_cast<u32x4*>(out + size_t(c.row_base + c.x0 + xl) * SW + v);
-#pragma unroll
-    for (int q = 0; q < 4; ++q)
-#pragma unroll
-      for (int cc = 0; cc < 3; ++cc)
-        __builtin_nontemporal_store(__builtin_bit_cast(u32x4, make_double2(acc[q][cc].r, acc[q][cc].i)),
-                                    o + (q * 3 + cc) * NV);
-  }
-}
-
-// Chunk length of the register-staged D_B (C64; N_v = 4, 8, 12, 16, 24), or 0
+// Chunk length of the row-staged kernels (C64; N_v = 4, 8, 12, 16, 24), or 0
 // when the configuration is not covered.
 static int brillouin_rows_sites(int dtype, const Geom& g) {
   // FP32 only: the FP64 variant would not fit in registers
@@ -791,41 +554,12 @@ static int brillouin_rows_sites(int dtype, const Geom& g) {
   return R;
 }
 
-// Row-staged D_B: FP32 storage for N_v = 4, 8, 12, 16, 24 (the clover term for
-// N_v = 12 only), FP64 storage for N_v = 12.  Returns hipErrorNotSupported
-// when the configuration is not covered (the caller then uses the direct
-// kernel).  DSLASH_ROWS=0 disables it.
-hipError_t launch_brillouin_rows(bool adj, int dtype, const Geom& g, const void* Wl, const void* in, void* out,
-                                 double mass, hipStream_t st, const void* clover) {
-  if (knobs().rows.get(1) == 0) return hipErrorNotSupported;
-  if (!aligned16(Wl) || !aligned16(in) || !aligned16(out) || !aligned16(clover)) return hipErrorNotSupported;
-  if (dtype == DT_C128 && g.nv == 12 && !clover) {
-    // FP64: the direct-to-LDS staged kernel, chunks of 16 sites
-    const RowTraversal tr = make_row_traversal(g, uint32_t(kDmaSites), uint32_t(knobs().tband.get(2)));
-    const ChunkTiles o = bri_tiles(g, kDmaSites, 12L * 12 * long(sizeof(C128::word)));
-    const dim3 block(12, kDmaSites), grid(tr.rows_plane * uint32_t(g.n[2]) * uint32_t(g.n[3]));
-    const bool xcd = knobs().xcd.get(1) != 0;
-    const double diag = mass + 15.0 / 8.0;
-#define DSL_BD(A)                                                                                         \
-  hipLaunchKernelGGL((brillouin_rows_dma_kernel<A, 12>), grid, block, kDmaRowBytes, st, g, tr, o, int(xcd), \
-                     (const C128::word*)Wl, (const C128::word*)in, (C128::word*)out, diag)
-    if (adj) DSL_BD(true); else DSL_BD(false);
-#undef DSL_BD
-    return hipGetLastError();
-  }
-  const int R = brillouin_rows_sites(dtype, g);
-  if (R == 0 || (clover && g.nv != 12)) return hipErrorNotSupported;
-  int bt = 2;
-  bt = knobs().tband.get(bt);
-  bool xcd = true;
-  xcd = knobs().xcd.get(xcd) != 0;
-  switch (g.nv) {
-    case 4: return brillouin_rows_t<4, C64, float, false, false>(adj, g, R, bt, xcd, Wl, in, out, nullptr, mass, st);
-    case 8: return brillouin_rows_t<8, C64, float, false, false>(adj, g, R, bt, xcd, Wl, in, out, nullptr, mass, st);
-    case 16: return brillouin_rows_t<16, C64, float, false, false>(adj, g, R, bt, xcd, Wl, in, out, nullptr, mass, st);
-    case 24: return brillouin_rows_t<24, C64, float, false, false>(adj, g, R, bt, xcd, Wl, in, out, nullptr, mass, st);
-  }
-  return brillouin_rows_t<12, C64, float, false>(adj, g, R, bt, xcd, Wl, in, out, clover, mass, st);
+// What DSLASH_ROWS=2 asks for: FP32 storage at N_v = 4, 8, 12, 16, 24 (the clover
+// term at N_v = 12 only) where a chunk of one x-row holds its halo, FP64 storage
+// at N_v = 12.
+bool brillouin_rows_cover(int dtype, const Geom& g, bool clover) {
+  if (dtype == DT_C128) return g.nv == 12 && !clover;
+  return brillouin_rows_sites(dtype, g) > 0 && !(clover && g.nv != 12);
 }
 
 // D_B with the off-axis links built from V inside the row-staged kernel (no W
@@ -841,12 +575,12 @@ hipError_t launch_brillouin_fly(bool adj, int dtype, const Geom& g, const void* 
   bool xcd = true;
   xcd = knobs().xcd.get(xcd) != 0;
   switch (g.nv) {
-    case 4: return brillouin_rows_t<4, C64, float, true, false>(adj, g, R, bt, xcd, V, in, out, nullptr, mass, st);
-    case 8: return brillouin_rows_t<8, C64, float, true, false>(adj, g, R, bt, xcd, V, in, out, nullptr, mass, st);
-    case 16: return brillouin_rows_t<16, C64, float, true, false>(adj, g, R, bt, xcd, V, in, out, nullptr, mass, st);
-    case 24: return brillouin_rows_t<24, C64, float, true, false>(adj, g, R, bt, xcd, V, in, out, nullptr, mass, st);
+    case 4: return brillouin_rows_t<4, C64, float, false>(adj, g, R, bt, xcd, V, in, out, nullptr, mass, st);
+    case 8: return brillouin_rows_t<8, C64, float, false>(adj, g, R, bt, xcd, V, in, out, nullptr, mass, st);
+    case 16: return brillouin_rows_t<16, C64, float, false>(adj, g, R, bt, xcd, V, in, out, nullptr, mass, st);
+    case 24: return brillouin_rows_t<24, C64, float, false>(adj, g, R, bt, xcd, V, in, out, nullptr, mass, st);
   }
-  return brillouin_rows_t<12, C64, float, true>(adj, g, R, bt, xcd, V, in, out, clover, mass, st);
+  return brillouin_rows_t<12, C64, float>(adj, g, R, bt, xcd, V, in, out, clover, mass, st);
 }
 
 // Row-staged gradient with respect to W (FP32 storage, N_v = 4, 8, 12, 16,

@@ -24,7 +24,7 @@ struct Knob {
 struct Knobs {
   Knob sites_per_block, tband, xcd, row_sites, row_depth, tsteps, march_pp, rows, row_lds_extra, cg_fuse;
   Knob grad_tile_y, grad_tile_z, march_tile_y, march_tile_z, bri_tile_y, bri_tile_z, rows_tile_y,
-      rows_tile_z, blas_nt, wmarch_tile_y, wmarch_tile_z, flat_zb, flat_kb;
+      rows_tile_z, blas_nt, wmarch_tile_y, wmarch_tile_z, flat_zb, flat_kb, bri_lanes;
 };
 inline Knob read_knob(const char* name) {
   Knob k;
@@ -59,6 +59,7 @@ inline Knobs read_knobs() {
   r.wmarch_tile_z = read_knob("DSLASH_WMARCH_TILE_Z");
   r.flat_zb = read_knob("DSLASH_FLAT_ZB");
   r.flat_kb = read_knob("DSLASH_FLAT_KB");
+  r.bri_lanes = read_knob("DSLASH_BRI_LANES");
   return r;
 }
 inline Knobs& knob_store() {
@@ -97,6 +98,23 @@ hipError_t launch_apply(int op, bool adjoint, int dtype, const Geom& g, const vo
 hipError_t launch_wilson_rows(bool adjoint, int dtype, const Geom& g, const void* U, const void* in, void* out,
                               double mass, hipStream_t st, const void* clover = nullptr, bool compressed = false,
                               int epi = 0, EpiArgs* ea = nullptr);
+// Compute units of the current device (cached per device).
+inline int device_cus() {
+  static int cus[64] = {0};
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 256;
+  if (cus[dev] == 0) {
+    int n = 0;
+    if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0) n = 256;
+    cus[dev] = n;
+  }
+  return cus[dev];
+}
+
+// D_B for C64 and C128 at any N_v (brillouin_flat.hip); hipErrorNotSupported
+// otherwise.
+hipError_t launch_brillouin_flat(bool adjoint, int dtype, const Geom& g, const void* Wl, const void* in, void* out,
+                                 double mass, hipStream_t st, const void* clover);
 // D_W at any N_v, storage and alignment by the flat kernel (wilson_flat.hpp);
 // hipErrorNotSupported where a plane of sites reaches 4 GB, or for an epilogue
 // that does not fit.
@@ -106,8 +124,8 @@ hipError_t launch_wilson_flat(bool adjoint, int dtype, const Geom& g, const void
 hipError_t launch_staggered_rows(bool adjoint, int dtype, const Geom& g, const void* U, const void* in, void* out,
                                  double mass, hipStream_t st, bool compressed = false);
 hipError_t launch_compress_links(int dtype, size_t links, const void* V, void* Vc, hipStream_t st);
-hipError_t launch_brillouin_rows(bool adjoint, int dtype, const Geom& g, const void* W, const void* in, void* out,
-                                 double mass, hipStream_t st, const void* clover = nullptr);
+// What DSLASH_ROWS=2 asks of D_B (brillouin_rows.hip).
+bool brillouin_rows_cover(int dtype, const Geom& g, bool clover);
 hipError_t launch_brillouin_links(int dtype, const Geom& g, const void* V, void* W, hipStream_t st);
 hipError_t launch_brillouin_fly(bool adjoint, int dtype, const Geom& g, const void* V, const void* in, void* out,
                                 double mass, hipStream_t st, const void* clover = nullptr);

@@ -1,13 +1,13 @@
 """D_W where a workgroup's sites run across the ends of x-rows: the row-staged
 kernels on lattices whose rows hold no chunk of their own, at every N_v they take,
 and the direct kernel for FP64, the clover term, compressed links and 16-bit
-storage, at the edges of their chunks (planes smaller than a chunk, a last chunk of
+storage, and D_B, at the edges of their chunks (planes smaller than a chunk, a last chunk of
 one site, N_x = 2, columns past one workgroup) against the FP64 oracle, with the
 tolerances of the other operator tests."""
 import pytest
 
 import synthetic
-from oracle import clover, compress, evenodd, wilson
+from oracle import brillouin, clover, compress, evenodd, wilson
 from tests.gpu_util import compare, down, rounded, say, set_knob, up
 
 pytestmark = pytest.mark.gpu
@@ -128,3 +128,26 @@ def test_even_odd_hop_chunks_across_rows(dims, dt, nv):
         for adj in (False, True):
             compare(down(D.eo_hop(ue, uo, up(pin, dt), parity, adjoint=adj)), evenodd.hop_eo(u, pin, parity, adj), dt,
                     f"eo hop parity={parity} adj={adj}")
+
+
+# blocks of every width (N_v = 26, 40: several of them; odd N_v: words through
+# registers), planes smaller than a chunk, chunks of several rows, N_x = 2 and 3,
+# lattices that wrap in every direction within a chunk
+@pytest.mark.parametrize("dt,nvs", [("c64", [1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 12, 13, 16, 18, 22, 24, 26, 40]),
+                                    ("c128", [1, 2, 4, 5, 6, 7, 8, 10, 12, 17])])
+@pytest.mark.parametrize("dims", [(7, 5, 3, 4), (24, 2, 2, 3), (2, 9, 3, 2), (3, 4, 2, 3)])
+def test_brillouin_flat(dims, dt, nvs, monkeypatch):
+    set_knob(monkeypatch, "DSLASH_BRI_LANES", "0")  # small lattices would take the direct kernel in C64
+    v = synthetic.gauge_links(dims, "haar", 840)
+    w = rounded(brillouin.build(v), dt)
+    c = rounded(clover.pack(clover.term(v, 1.3)), dt)
+    W, C = up(w, dt), up(c, dt)
+    for nv in nvs:
+        say(f"case brillouin flat {dims} nv={nv} {dt}")
+        p = rounded(synthetic.wilson_spinor(dims, nv, 841 + nv), dt)
+        P = up(p, dt)
+        for adj in (False, True):
+            ref = brillouin.apply(w, p, 0.1, adj)
+            compare(down(D.apply("brillouin", W, P, 0.1, adjoint=adj)), ref, dt, f"D_B nv={nv} adj={adj}")
+        ref = brillouin.apply(w, p, 0.1, False) + clover.apply_term(clover.unpack(c), p)
+        compare(down(D.apply("brillouin", W, P, 0.1, clover=C)), ref, dt, f"D_B + C nv={nv}")
