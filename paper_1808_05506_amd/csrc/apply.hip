@@ -171,6 +171,8 @@ hipError_t launch_apply(int op, bool adj, int dtype, const Geom& g, const void* 
       if (clover) return hipErrorInvalidValue;
       const hipError_t e = launch_staggered_rows(adj, dtype, g, U, in, out, mass, st, compressed);
       if (e != hipErrorNotSupported || rows_only) return e;
+      const hipError_t f = launch_staggered_flat(adj, dtype, g, U, in, out, mass, st, compressed);
+      if (f != hipErrorNotSupported) return f;
       return apply_op<OP_STAGGERED>(adj, dtype, g, U, in, out, nullptr, mass, compressed, st);
     }
     case OP_WILSON: {

@@ -121,6 +121,10 @@ hipError_t launch_brillouin_flat(bool adjoint, int dtype, const Geom& g, const v
 hipError_t launch_wilson_flat(bool adjoint, int dtype, const Geom& g, const void* U, const void* in, void* out,
                               double mass, hipStream_t st, const void* clover, bool compressed, int epi = 0,
                               EpiArgs* ea = nullptr);
+// D_S at any N_v, storage and alignment (staggered_flat.hip); hipErrorNotSupported
+// where a plane of sites reaches 4 GB.
+hipError_t launch_staggered_flat(bool adjoint, int dtype, const Geom& g, const void* U, const void* in, void* out,
+                                 double mass, hipStream_t st, bool compressed);
 hipError_t launch_staggered_rows(bool adjoint, int dtype, const Geom& g, const void* U, const void* in, void* out,
                                  double mass, hipStream_t st, bool compressed = false);
 hipError_t launch_compress_links(int dtype, size_t links, const void* V, void* Vc, hipStream_t st);

@@ -13,7 +13,7 @@ namespace dsl {
 // 3 planes x 7 of 28 chunks at two workgroups a CU, 1167 at three, 1368 with four
 // and the tile of the smallest surface; 16^3 x 32: 220 us with 2 whole planes, 230
 // with 4 planes x 7 of 13 chunks, 242 and 272 as before.
-FlatShape flat_shape(const Geom& g, int word_bytes, int vw, int lw, bool clover) {
+FlatShape flat_shape(const Geom& g, int comps, int word_bytes, int vw, int lw, bool clover) {
   FlatShape s{};
   const uint32_t plane = uint32_t(g.n[0]) * uint32_t(g.n[1]);
   const uint32_t groups = uint32_t(g.nv / vw), gb = groups < 256 ? groups : 256;
@@ -34,7 +34,7 @@ FlatShape flat_shape(const Geom& g, int word_bytes, int vw, int lw, bool clover)
   s.o.P = best;
   s.o.chunks = (plane + best - 1) / best;
   s.o.groups = FastDiv::make(gb);
-  const double row = 12.0 * g.nv * word_bytes * best, full = row * s.o.chunks;
+  const double row = double(comps) * g.nv * word_bytes * best, full = row * s.o.chunks;
   if (full <= 0.6 * 1024 * 1024) {
     s.o.kb = s.o.chunks;
     s.o.zb = uint32_t(1.2 * 1024 * 1024 / full);
@@ -50,7 +50,7 @@ FlatShape flat_shape(const Geom& g, int word_bytes, int vw, int lw, bool clover)
   s.grid = dim3(s.o.chunks * uint32_t(g.n[2]) * uint32_t(g.n[3]), (groups + gb - 1) / gb);
   s.block = dim3(best * gb);
   s.lds = size_t(best) * site_lds;
-  if (word_bytes == 16 && s.lds < 79 * 1024) s.lds = 79 * 1024;
+  if (comps == 12 && word_bytes == 16 && s.lds < 79 * 1024) s.lds = 79 * 1024;
   if (s.lds < size_t(knobs().row_lds_extra.get(0))) s.lds = size_t(knobs().row_lds_extra.get(0));
   return s;
 }

@@ -414,7 +414,8 @@ struct FlatShape {
   dim3 grid, block;
   size_t lds;
 };
-FlatShape flat_shape(const Geom& g, int word_bytes, int vw, int lw, bool clover);
+// comps: spinor components of a site (12, D_S 3).
+FlatShape flat_shape(const Geom& g, int comps, int word_bytes, int vw, int lw, bool clover);
 
 // Columns per lane: as many as 16 bytes hold and N_v is a multiple of; one for
 // fields off a 16-byte boundary.
@@ -439,7 +440,7 @@ struct FlatArgs {
 template <bool EO, bool ADJ, bool CLOV, int LW, int EPI, class S, class T, int VW, int NVC>
 static hipError_t flat_launch(const Geom& g, const FlatArgs& a, hipStream_t st, EpiArgs& ea) {
   using W = typename S::word;
-  const FlatShape s = flat_shape(g, int(sizeof(W)), VW, LW, CLOV);
+  const FlatShape s = flat_shape(g, 12, int(sizeof(W)), VW, LW, CLOV);
   if (EPI != EPI_STORE) {
     if (s.grid.y > 1 || s.grid.x > ea.capacity) return hipErrorNotSupported;
     ea.blocks = s.grid.x;

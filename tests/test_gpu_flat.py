@@ -1,13 +1,13 @@
-"""D_W where a workgroup's sites run across the ends of x-rows: the row-staged
-kernels on lattices whose rows hold no chunk of their own, at every N_v they take,
-and the direct kernel for FP64, the clover term, compressed links and 16-bit
-storage, and D_B, at the edges of their chunks (planes smaller than a chunk, a last chunk of
-one site, N_x = 2, columns past one workgroup) against the FP64 oracle, with the
-tolerances of the other operator tests."""
+"""The operators where a workgroup's sites run across the ends of x-rows: the
+row-staged D_W kernels on lattices whose rows hold no chunk of their own, at every
+N_v they take, the direct D_W kernel for FP64, the clover term, compressed links
+and 16-bit storage, D_B, and D_S, at the edges of their chunks (planes smaller than
+a chunk, a last chunk of one site, N_x = 2, columns past one workgroup) against the
+FP64 oracle, with the tolerances of the other operator tests."""
 import pytest
 
 import synthetic
-from oracle import brillouin, clover, compress, evenodd, wilson
+from oracle import brillouin, clover, compress, evenodd, staggered, wilson
 from tests.gpu_util import compare, down, rounded, say, set_knob, up
 
 pytestmark = pytest.mark.gpu
@@ -151,3 +151,22 @@ def test_brillouin_flat(dims, dt, nvs, monkeypatch):
             compare(down(D.apply("brillouin", W, P, 0.1, adjoint=adj)), ref, dt, f"D_B nv={nv} adj={adj}")
         ref = brillouin.apply(w, p, 0.1, False) + clover.apply_term(clover.unpack(c), p)
         compare(down(D.apply("brillouin", W, P, 0.1, clover=C)), ref, dt, f"D_B + C nv={nv}")
+
+
+@pytest.mark.parametrize("dt,nvs", [("c64", [1, 2, 5, 8, 12, 13, 24, 300]), ("c128", [1, 3, 12, 24]),
+                                    ("bf16", [1, 2, 4, 6, 12]), ("f16", [3, 4, 10, 12])])
+@pytest.mark.parametrize("dims", [(10, 4, 2, 4), (2, 6, 4, 2), (4, 2, 2, 6), (38, 2, 4, 2)])
+def test_staggered_flat(dims, dt, nvs, monkeypatch):
+    set_knob(monkeypatch, "DSLASH_ROWS", "0")  # rows of whole chunks as well
+    u = rounded(synthetic.gauge_links(dims, "haar", 860), dt)
+    vc = rounded(compress.compress(synthetic.gauge_links(dims, "smooth", 861)), dt)
+    U, VC = up(u, dt), up(vc, dt)
+    for nv in nvs:
+        say(f"case staggered flat {dims} nv={nv} {dt}")
+        p = rounded(synthetic.staggered_spinor(dims, nv, 862 + nv), dt)
+        P = up(p, dt)
+        for adj in (False, True):
+            compare(down(D.apply("staggered", U, P, 0.1, adjoint=adj)), staggered.apply(u, p, 0.1, adj), dt,
+                    f"D_S nv={nv} adj={adj}")
+        compare(down(D.apply_compressed("staggered", VC, P, 0.1)), compress.apply("staggered", vc, p, 0.1, False), dt,
+                f"D_S compressed nv={nv}")
