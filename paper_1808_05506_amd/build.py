@@ -22,7 +22,7 @@ BUILD = os.path.join(ROOT, "_build")
 LIB = os.path.join(HERE, "libdslash.so")
 ARCH = "gfx950"
 
-SOURCES = ["apply.hip", "apply_rows.hip", "wilson_rows_c64.hip", "wilson_rows_bf16.hip", "wilson_rows_f16.hip", "wilson_rows_any.hip", "wilson_flat.hip", "wilson_flat16.hip", "staggered_flat.hip", "staggered_rows.hip", "brillouin_flat.hip", "brillouin_rows.hip", "grad_rows.hip", "links_grad.hip", "eo.hip", "clover.hip", "bri_grad.hip", "blas.hip", "capi.cpp", "solver.cpp"]
+SOURCES = ["apply.hip", "apply_rows.hip", "wilson_rows_c64.hip", "wilson_rows_bf16.hip", "wilson_rows_f16.hip", "wilson_rows_any.hip", "wilson_flat.hip", "wilson_flat16.hip", "staggered_flat.hip", "staggered_rows.hip", "brillouin_flat.hip", "brillouin_wgrad.hip", "brillouin_rows.hip", "grad_rows.hip", "links_grad.hip", "eo.hip", "clover.hip", "bri_grad.hip", "blas.hip", "capi.cpp", "solver.cpp"]
 
 FLAGS = [
     "-x", "hip", f"--offload-arch={ARCH}", "-O3", "-std=c++17", "-fPIC",

@@ -27,21 +27,11 @@
 // 32^4, N_v = 12, C64: 6.20 ms (6.94 before, hop by hop and staged through
 // registers; with the staging left out 4.67); 16^3 x 32, C128: 1.39 ms (2.12;
 // 1.09).  C64 chunks of 21 sites: 6.23 ms, of 16: 6.26; C128 of 20: 1.41, of 16 1.50.
-#include "chunks.hpp"
-#include "launch.hpp"
-#include "rows.hpp"
-#include "stencils.hpp"
-#include "tiles.hpp"
+#include "bri_runs.hpp"
 
 namespace dsl {
 
 namespace {
-
-constexpr int kRuns = 27;  // (dy, dz, dt) in {-1, 0, 1}^3 = r % 3, r / 3 % 3, r / 9; run 13 is the own one
-
-// How a run gets into LDS: C128 words or C64 pairs of columns straight from
-// global memory, C64 words through registers (odd N_v, pointers off 16 bytes).
-enum { BRI_WIDE, BRI_PAIRS, BRI_WORDS };
 
 template <class S, int NB_, int P_, int MODE_>
 struct BriBlock {
@@ -51,16 +41,6 @@ struct BriBlock {
   static constexpr int KL = (9 * P + LANES - 1) / LANES;      // link words per lane and column
   static constexpr int WAVES = MODE == BRI_PAIRS && NB > 4 ? 3 : 2;  // per SIMD
 };
-
-DSL_HD uint32_t shift_y(uint32_t p, int dy, uint32_t nx, uint32_t nxy) {
-  if (dy > 0) return p + nx < nxy ? p + nx : p + nx - nxy;
-  if (dy < 0) return p >= nx ? p - nx : p + nxy - nx;
-  return p;
-}
-
-__device__ __forceinline__ void dma16(const void* src, void* lds_wave_base) {
-  __builtin_amdgcn_global_load_lds(src, (__attribute__((address_space(3))) void*)lds_wave_base, 16, 0, 0);
-}
 
 template <bool DAG, class S, class T>
 __device__ __forceinline__ void lds_link(const typename S::word* link, cpx<T> (&u)[3][3]) {
@@ -191,48 +171,13 @@ __global__ void __launch_bounds__(B::LANES, B::WAVES)
 
   uint32_t seg;
   const FlatChunk<4> c = flat_chunk<4>(g, m, xcd_block(blockIdx.x, gridDim.x, xcd != 0), seg);
-  const int nv = g.nv, tid = int(threadIdx.x);
-  const int xl = tid / NB, v = tid - xl * NB;
-  const int v0 = int(blockIdx.y) * NB, vc = v0 + v < nv ? v0 + v : nv - 1;  // column of the lane
-  const int i = xl < c.n ? xl : c.n - 1;
-  const uint32_t nx = c.nx, nxy = c.nxy, p = c.p0 + uint32_t(i);
-  const uint32_t site_bytes = uint32_t(12 * nv * WB), comp_bytes = uint32_t(nv * WB);
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
-
-  // LDS slots of x - 1, x, x + 1 (x_slots numbers the chunk from 1, halo site k
-  // as 0 or P + k)
+  RunStage<B, S> st;
+  st.init(g, c, int(blockIdx.y) * NB);
+  const int nv = g.nv, tid = st.tid, wave = st.wave;
+  const uint32_t nx = c.nx, nxy = c.nxy, p = st.p;
   int ps[3];
-  {
-    const XSlots xs = x_slots(g, c, P, i);
-    ps[0] = (xs.b == 0 ? P : (xs.b > P ? xs.b : xs.b - 1)) * NB + v;
-    ps[1] = i * NB + v;
-    ps[2] = (xs.f > P ? xs.f : xs.f - 1) * NB + v;
-  }
-  const W* const link = wbuf + i * 9;
-
-  // Site q of a run seen from site p of the chunk's plane: shift_y(p, dy).
-  // PAIRS: piece tid + j LANES of half a run's [6][P + 4][NB / 2] pairs of columns,
-  // its byte offset at dy = 0 and whether y + 1 (bit j) and y - 1 (bit 16 + j) wrap.
-  constexpr int HP = 6 * PL / 2, NJ = (HP + LANES - 1) / LANES;
-  uint32_t pj[B::MODE == BRI_PAIRS ? NJ : 1], wrap = 0;
-  if constexpr (B::MODE == BRI_PAIRS) {
-    static_assert(NJ <= 16, "one mask");
-#pragma unroll
-    for (int j = 0; j < NJ; ++j) {
-      const int h = tid + j * LANES, comp = h / (PL / 2), rem = h - comp * (PL / 2);
-      const int slot = rem / (NB / 2), col = v0 + 2 * (rem - slot * (NB / 2));
-      const uint32_t q = slot < P ? c.p0 + uint32_t(slot < c.n ? slot : c.n - 1) : halo_site(c, slot - P);
-      pj[j] = q * site_bytes + uint32_t(comp < 6 ? comp : 5) * comp_bytes + uint32_t(col < nv ? col : nv - 2) * WB;
-      wrap |= (q + nx >= nxy ? 1u : 0u) << j | (q < nx ? 1u : 0u) << (16 + j);
-    }
-  }
-  // else the lane's own column and site, and of the halo sites (4 NB lanes of a
-  // wave, component by component; or the lane's share of the 24 NB words of a half)
-  const uint32_t soff = uint32_t(vc * WB);
-  constexpr int HK = (24 * NB + LANES - 1) / LANES;
-  const int hs = lane / NB;
-  const uint32_t hq = halo_site(c, hs & 3);
-  const uint32_t hoff = uint32_t((v0 + lane - hs * NB < nv ? v0 + lane - hs * NB : nv - 1) * WB);
+  st.slots(g, c, ps);
+  const W* const link = wbuf + st.i * 9;
 
   // link words: element e of chunk site s, and of its x neighbours
   uint32_t lq[B::KL][3], le[B::KL];
@@ -252,14 +197,7 @@ __global__ void __launch_bounds__(B::LANES, B::WAVES)
 #pragma unroll
     for (int b = 0; b < 3; ++b) acc[q][b] = zero<T>();
 
-  W row[B::MODE == BRI_WORDS ? 6 : 1], halo[B::MODE == BRI_WORDS ? HK : 1], lw[B::KL][3];
-  // run r: (dy, dz, dt) and its plane
-#define DSL_RUN(r)                                                              \
-  const int dt = (r) / 9 - 1, dz = (r) / 3 % 3 - 1, dy = (r) % 3 - 1;           \
-  int z_ = c.z + dz, t_ = c.t + dt;                                             \
-  z_ = z_ < 0 ? z_ + g.n[2] : (z_ >= g.n[2] ? z_ - g.n[2] : z_);                \
-  t_ = t_ < 0 ? t_ + g.n[3] : (t_ >= g.n[3] ? t_ - g.n[3] : t_);                \
-  const uint32_t plane = nxy * (uint32_t(z_) + uint32_t(g.n[2]) * uint32_t(t_));
+  W lw[B::KL][3];
   // the lane's word k of link column col of run r
   const auto link_word = [&](int r, uint32_t plane, int dy, int col, int k) {
     const bool dag = 3 * r + col <= 40;
@@ -271,7 +209,8 @@ __global__ void __launch_bounds__(B::LANES, B::WAVES)
   };
   // links of run r: requested (WIDE: into LDS, else into registers) ...
   const auto links = [&](int r) {
-    DSL_RUN(r)
+    const uint32_t plane = run_plane(g, c, r);
+    const int dy = r % 3 - 1;
 #pragma unroll
     for (int k = 0; k < B::KL; ++k)
       if (tid + k * LANES < 9 * P) {
@@ -299,53 +238,6 @@ __global__ void __launch_bounds__(B::LANES, B::WAVES)
         }
       }
   };
-  // spins 2 h, 2 h + 1 of run r: requested (WORDS: into registers, else into LDS) ...
-  const auto half = [&](int r, int h, W* dst) {
-    DSL_RUN(r)
-    const char* const src =
-        reinterpret_cast<const char*>(in) + size_t(plane) * site_bytes + size_t(6 * h) * comp_bytes;
-    if constexpr (B::MODE == BRI_PAIRS) {
-      const uint32_t step = dy > 0 ? nx * site_bytes : (dy < 0 ? 0u - nx * site_bytes : 0u);
-      const uint32_t over = dy > 0 ? (nx - nxy) * site_bytes : (dy < 0 ? (nxy - nx) * site_bytes : 0u);
-      const uint32_t bits = dy < 0 ? wrap >> 16 : wrap;
-#pragma unroll
-      for (int j = 0; j < NJ; ++j)
-        if (tid + j * LANES < HP)
-          dma16(src + uint32_t(pj[j] + (bits >> j & 1 ? over : step)), dst + 2 * (j * LANES + wave * 64));
-    } else {
-      const char* s0 = src + (shift_y(p, dy, nx, nxy) * site_bytes + soff);
-#pragma unroll
-      for (int j = 0; j < 6; ++j) {
-        if constexpr (B::MODE == BRI_WIDE) dma16(s0 + size_t(j) * comp_bytes, dst + j * PL + wave * 64);
-        else row[j] = *reinterpret_cast<const W*>(s0 + size_t(j) * comp_bytes);
-      }
-      if constexpr (B::MODE == BRI_WIDE) {
-        if (lane < 4 * NB) {
-          const char* h0 = src + (shift_y(hq, dy, nx, nxy) * site_bytes + hoff);
-          for (int j = wave; j < 6; j += (LANES + 63) / 64) dma16(h0 + size_t(j) * comp_bytes, dst + j * PL + P * NB);
-        }
-      } else {
-#pragma unroll
-        for (int k = 0; k < HK; ++k) {
-          const int w = tid + k * LANES, comp = w / (4 * NB), rem = w - comp * 4 * NB, hk = rem / NB;
-          const int col = v0 + rem - hk * NB;
-          halo[k] = *reinterpret_cast<const W*>(src + (shift_y(halo_site(c, hk), dy, nx, nxy) * site_bytes +
-                                                       uint32_t(comp < 6 ? comp : 5) * comp_bytes +
-                                                       uint32_t((col < nv ? col : nv - 1) * WB)));
-        }
-      }
-    }
-  };
-  // ... and from the registers into LDS
-  const auto half_commit = [&](W* dst) {
-#pragma unroll
-    for (int j = 0; j < 6; ++j) dst[j * PL + i * NB + v] = row[j];
-#pragma unroll
-    for (int k = 0; k < HK; ++k) {
-      const int w = tid + k * LANES, comp = w / (4 * NB);
-      if (comp < 6) dst[comp * PL + P * NB + w - comp * 4 * NB] = halo[k];
-    }
-  };
   // Half a run is in flight while the other one is applied.  Before the first
   // barrier of run r its spins 0, 1 and its links have arrived; then spins 2, 3 are
   // fetched, and after the second barrier (the links are in registers) spins 0, 1
@@ -353,10 +245,10 @@ __global__ void __launch_bounds__(B::LANES, B::WAVES)
   // passes through registers is requested one half earlier.
 #define DSL_FETCH0(r)                              \
   if constexpr (B::MODE == BRI_WORDS) {            \
-    half_commit(buf0);                              \
-    half(r, 1, buf1);                              \
+    st.half_commit(buf0);                              \
+    st.half(g, c, in, r, 1, buf1);                              \
   } else {                                         \
-    half(r, 0, buf0);                              \
+    st.half(g, c, in, r, 0, buf0);                              \
   }                                                \
   if constexpr (B::MODE == BRI_WIDE) {             \
     links(r);                                      \
@@ -366,10 +258,10 @@ __global__ void __launch_bounds__(B::LANES, B::WAVES)
   }
 #define DSL_FETCH1(r)                                  \
   if constexpr (B::MODE == BRI_WORDS) {                \
-    half_commit(buf1);                                  \
-    half((r) + 1 < kRuns ? (r) + 1 : kRuns - 1, 0, buf0); \
+    st.half_commit(buf1);                                  \
+    st.half(g, c, in, (r) + 1 < kRuns ? (r) + 1 : kRuns - 1, 0, buf0); \
   } else {                                             \
-    half(r, 1, buf1);                                  \
+    st.half(g, c, in, r, 1, buf1);                                  \
   }
 #define DSL_BARRIER                                                   \
   if constexpr (B::MODE != BRI_WORDS) __builtin_amdgcn_s_waitcnt(0);  \
@@ -386,7 +278,7 @@ __global__ void __launch_bounds__(B::LANES, B::WAVES)
     DSL_FETCH0((r) + 1 < kRuns ? (r) + 1 : kRuns - 1)                                                       \
     run_spins<2, ADJ, OWN, B, S, T>(buf1, ps, u, dy, dz, dt, acc);                                          \
   }
-  if constexpr (B::MODE == BRI_WORDS) half(0, 0, buf0);
+  if constexpr (B::MODE == BRI_WORDS) st.half(g, c, in, 0, 0, buf0);
   if constexpr (B::MODE != BRI_WIDE) links(0);
   DSL_FETCH0(0)
 #pragma nounroll
@@ -398,10 +290,9 @@ __global__ void __launch_bounds__(B::LANES, B::WAVES)
 #undef DSL_BARRIER
 #undef DSL_FETCH0
 #undef DSL_FETCH1
-#undef DSL_RUN
   // the diagonal term last, from memory: the sums before it stay small (error
   // against FP64 in C64, relative: 6e-8; 1.9e-7 with it between the hops)
-  const size_t base = size_t(c.plane + p) * 12 * nv + vc;
+  const size_t base = size_t(c.plane + p) * 12 * nv + st.vc;
   cpx<T> own[4][3];
   load_wspinor<S, T>(in, base, nv, own);
 #pragma unroll
@@ -409,7 +300,7 @@ __global__ void __launch_bounds__(B::LANES, B::WAVES)
 #pragma unroll
     for (int b = 0; b < 3; ++b) acc[q][b] = rmadd(acc[q][b], diag, own[q][b]);
   if constexpr (CLOV) clover_madd<S, T>(C + size_t(c.plane + p) * 36, own, acc);
-  if (xl < c.n && v0 + v < nv) {
+  if (st.xl < c.n && st.v0 + st.v < nv) {
 #pragma unroll
     for (int q = 0; q < 4; ++q)
 #pragma unroll
@@ -483,18 +374,7 @@ hipError_t launch_brillouin_flat(bool adj, int dtype, const Geom& g, const void*
   if (dtype == DT_C128 && !(aligned16(Wl) && aligned16(in) && aligned16(out) && aligned16(clover)))
     return hipErrorNotSupported;
   const BriCall a{adj, &g, Wl, in, clover, out, mass, st};
-  // the block with the fewest idle columns, the wider one of equals
-  static const int widths64[] = {24, 16, 12, 10, 8, 6, 4}, widths128[] = {12, 8, 6, 4};
-  const int* w = dtype == DT_C64 ? widths64 : widths128;
-  const int nw = dtype == DT_C64 ? 7 : 4;
-  int nb = w[0], cols = 0;
-  for (int k = 0; k < nw; ++k) {
-    const int n = (g.nv + w[k] - 1) / w[k] * w[k];
-    if (cols == 0 || n < cols) {
-      cols = n;
-      nb = w[k];
-    }
-  }
+  const int nb = bri_block(dtype, g.nv);
   if (dtype == DT_C64) {
     const bool pairs = g.nv % 2 == 0 && aligned16(in);
     switch (nb) {

@@ -1,5 +1,5 @@
 // Row-staged D_B with its off-axis links built on the fly (Sec. 5; see rows.hpp for
-// the row staging), and the gradient with respect to W.  A workgroup
+// the row staging).  A workgroup
 // owns an x-row chunk of R sites and all N_v right-hand sides (thread (x, v)).
 // The 80 hops of the 3^4 stencil reach the 27 rows (y + dy, z + dz, t + dt),
 // dy, dz, dt in {-1, 0, 1}; each such row is staged once, with the halo sites
@@ -34,9 +34,6 @@ DSL_HD uint32_t bri_row_base(const Geom& g, const RowChunk& c, int dy, int dz, i
   t = t < 0 ? t + g.n[3] : (t >= g.n[3] ? t - g.n[3] : t);
   return uint32_t(g.stride[1] * y + g.stride[2] * z + g.stride[3] * t);
 }
-
-// base-3 code n(d) = sum_mu (d_mu + 1) 3^mu; d is stored (in slot n - 41) iff n > 40
-DSL_HD int bri_code(int dx, int dy, int dz, int dt) { return (dx + 1) + 3 * (dy + 1) + 9 * (dz + 1) + 27 * (dt + 1); }
 
 template <int NV, class S>
 struct BriStage {
@@ -317,11 +314,10 @@ __global__ void __launch_bounds__(256, BriWaves<NV>::value)
 // equal sizes, by >= bz on a tie; DSLASH_BRI_TILE_Y, _Z override (0: t-band
 // order).  Each output row stages the 27 rows around it, and in the t-band
 // order its +-z rows were a band of planes away, gone from the XCD's L2: 32^4,
-// N_v = 12, 23.8 against 24.5 ms.  The W-gradient kernel gained nothing (6.96
-// ms either way) and keeps the t-band order (tiled = false).
-static ChunkTiles bri_tiles(const Geom& g, int R, long site_bytes, bool tiled = true) {
+// N_v = 12, 23.8 against 24.5 ms.
+static ChunkTiles bri_tiles(const Geom& g, int R, long site_bytes) {
   int by, bz;
-  pick_tile(g, long((g.n[0] + R - 1) / R) * R * site_bytes, tiled ? 1280L * 1024 : 0, by, bz);
+  pick_tile(g, long((g.n[0] + R - 1) / R) * R * site_bytes, 1280L * 1024, by, bz);
   return make_chunk_tiles(g, R, knobs().bri_tile_y.get(by), knobs().bri_tile_z.get(bz));
 }
 
@@ -350,191 +346,6 @@ static hipError_t brillouin_rows_t(bool adj, const Geom& g, int R, int bt, bool 
     if (adj) DSL_BK(true, false); else DSL_BK(false, false);
   }
 #undef DSL_BK
-  return hipGetLastError();
-}
-
-// ---------------------------------------------------------------- gradient with respect to W
-// G_{W_d}(x) for the 40 stored directions d (slot n(d) - 41): the derivative
-// of L = Re sum conj(chi) (D_B psi) with each W taken as a free complex matrix.
-// W_d(x) enters the hop of d into out(x) with the spin factor S_d =
-// a_k + b_k d.gamma, and, as W_{-d}(x + d) = W_d(x)^dag, the hop of -d into
-// out(x + d) with S_{-d} = a_k - b_k d.gamma (eqs. def_der, def_lap, Tab. 1).
-// Both factors are Hermitian, so
-//   G_{W_d}(x) = sum_v sum_s [ chi(x)_s (x) conj((S_d psi(x + d))_s)
-//                            + psi(x)_s (x) conj((S_{-d} chi(x + d))_s) ].
-// The stored d reach the 14 rows 13 .. 26 of the 27-row order (the own row
-// for d = +x only, then every row with (dt, dz, dy) lexicographically
-// positive, where all three dx are stored).  A workgroup owns an x-row chunk;
-// each row's psi run, then its chi run, with the halo sites x0 - 1 and x0 + n,
-// pass through one LDS buffer.  Lane (x, v) keeps chi(x), psi(x) of its
-// right-hand side in registers; it forms the first term of each of the row's
-// directions from the psi run and adds the second from the chi run, in its own
-// LDS slots.  The N_v shares of a site are then summed in lane order
-// (deterministic, no atomics) and written to G_W.  One run at a time keeps the
-// kernel at 160 VGPRs, three waves per SIMD.
-
-constexpr int kWgFirstRow = 13;  // the own row; rows 13 .. 26 hold every stored d
-
-// out = (a + sum_mu B_mu gamma_mu) in, B_mu = b d_mu: the spin factor of a
-// hop, in the chiral basis of bri_hop; the d_mu tests are uniform.
-template <class T>
-__device__ __forceinline__ void bri_spin(T a, T B1, T B2, T B3, T B4, int d0, int d1, int d2, int d3,
-                                         const cpx<T> (&in)[4][3], cpx<T> (&out)[4][3]) {
-#pragma unroll
-  for (int q = 0; q < 4; ++q)
-#pragma unroll
-    for (int cc = 0; cc < 3; ++cc) out[q][cc] = mk(a * in[q][cc].r, a * in[q][cc].i);
-#pragma unroll
-  for (int cc = 0; cc < 3; ++cc) {
-    if (__builtin_amdgcn_readfirstlane(d3) != 0) {
-      out[0][cc] = rmadd(out[0][cc], B4, in[2][cc]);
-      out[1][cc] = rmadd(out[1][cc], B4, in[3][cc]);
-      out[2][cc] = rmadd(out[2][cc], B4, in[0][cc]);
-      out[3][cc] = rmadd(out[3][cc], B4, in[1][cc]);
-    }
-    if (__builtin_amdgcn_readfirstlane(d2) != 0) {
-      out[0][cc] = cmadd_i(out[0][cc], -B3, in[2][cc]);
-      out[1][cc] = cmadd_i(out[1][cc], B3, in[3][cc]);
-      out[2][cc] = cmadd_i(out[2][cc], B3, in[0][cc]);
-      out[3][cc] = cmadd_i(out[3][cc], -B3, in[1][cc]);
-    }
-    if (__builtin_amdgcn_readfirstlane(d1) != 0) {
-      out[0][cc] = rmadd(out[0][cc], -B2, in[3][cc]);
-      out[1][cc] = rmadd(out[1][cc], B2, in[2][cc]);
-      out[2][cc] = rmadd(out[2][cc], B2, in[1][cc]);
-      out[3][cc] = rmadd(out[3][cc], -B2, in[0][cc]);
-    }
-    if (__builtin_amdgcn_readfirstlane(d0) != 0) {
-      out[0][cc] = cmadd_i(out[0][cc], -B1, in[3][cc]);
-      out[1][cc] = cmadd_i(out[1][cc], -B1, in[2][cc]);
-      out[2][cc] = cmadd_i(out[2][cc], B1, in[1][cc]);
-      out[3][cc] = cmadd_i(out[3][cc], B1, in[0][cc]);
-    }
-  }
-}
-
-// gm += sum_s l_s (x) conj(r_s)
-template <class T>
-__device__ __forceinline__ void bri_outer(const cpx<T> (&l)[4][3], const cpx<T> (&r)[4][3], cpx<T> (&gm)[3][3]) {
-#pragma unroll
-  for (int s = 0; s < 4; ++s)
-#pragma unroll
-    for (int a = 0; a < 3; ++a)
-#pragma unroll
-      for (int b = 0; b < 3; ++b) gm[a][b] = cmaddj(gm[a][b], l[s][a], r[s][b]);
-}
-
-template <int NV, class S, class T>
-__device__ __forceinline__ void bri_lds_spinor(const typename S::word* site, int v, cpx<T> (&p)[4][3]) {
-#pragma unroll
-  for (int q = 0; q < 4; ++q)
-#pragma unroll
-    for (int cc = 0; cc < 3; ++cc) p[q][cc] = S::template load<T>(site + (q * 3 + cc) * NV + v);
-}
-
-template <int NV, class S, class T>
-__global__ void __launch_bounds__(256, 3)
-    bri_wgrad_rows_kernel(Geom g, RowTraversal tr, ChunkTiles o, int xcd, const typename S::word* __restrict__ chi,
-                          const typename S::word* __restrict__ psi, typename S::word* __restrict__ GW) {
-  using W = typename S::word;
-  constexpr int SSW = SiteStride<NV, S>::WORDS;
-  extern __shared__ uint4 smem_wg[];
-  const int R = int(tr.sb);
-  W* bs = reinterpret_cast<W*>(smem_wg);              // one staged run, (R + 2) sites
-  T* red = reinterpret_cast<T*>(bs + (R + 2) * SSW);  // [3][R][18][NV]
-
-  const uint32_t L = xcd_block(blockIdx.x, gridDim.x, xcd != 0);
-  const RowChunk c = order_chunk(g, tr, o, L);
-  const int v = threadIdx.x, xl = threadIdx.y;
-  const int tid = xl * NV + v, nth = R * NV;
-  const int xm = wrap_x(g, c.x0 - 1), xp = wrap_x(g, c.x0 + c.n);
-  const int xc = xl < c.n ? xl : c.n - 1;
-
-  cpx<T> ox[4][3], op[4][3];  // chi(x), psi(x) of the lane, read once from global memory
-  {
-    const size_t base = size_t(c.row_base + c.x0 + xc) * 12 * NV + v;
-#pragma unroll
-    for (int q = 0; q < 4; ++q)
-#pragma unroll
-      for (int cc = 0; cc < 3; ++cc) {
-        ox[q][cc] = S::template load<T>(chi + base + (q * 3 + cc) * NV);
-        op[q][cc] = S::template load<T>(psi + base + (q * 3 + cc) * NV);
-      }
-  }
-  BriRowRegs<NV, S> qr;
-  bri_issue<NV, S>(g, c, psi, kWgFirstRow, xm, xp, xl, v, tid, nth, qr);
-#pragma nounroll
-  for (int r = kWgFirstRow; r < kBriRows; ++r) {
-    int dy, dz, dt;
-    bri_row_offset(r, dy, dz, dt);
-#pragma unroll
-    for (int phase = 0; phase < 2; ++phase) {
-      // phase 0 stages psi of the row, phase 1 chi; each requests the next run
-      __syncthreads();  // the staged run and the sums of the previous phase or row are read
-      bri_commit<NV, S>(c, qr, bs, xl, v, tid, nth);
-      __syncthreads();
-      const int rn = phase == 0 ? r : (r + 1 < kBriRows ? r + 1 : kBriRows - 1);
-      bri_issue<NV, S>(g, c, phase == 0 ? chi : psi, rn, xm, xp, xl, v, tid, nth, qr);
-#pragma unroll
-      for (int dx = -1; dx <= 1; ++dx) {
-        if (r == kWgFirstRow && dx != 1) continue;
-        const int k = (dx != 0) + (dy != 0) + (dz != 0) + (dt != 0);
-        const T a = T(-0.5) * bri_lambda<T>(k), b = (phase == 0 ? T(1) : T(-1)) * bri_rho<T>(k);
-        cpx<T> gm[3][3];
-#pragma unroll
-        for (int i = 0; i < 3; ++i)
-#pragma unroll
-          for (int j = 0; j < 3; ++j) gm[i][j] = zero<T>();
-        cpx<T> f[4][3], sf[4][3];
-        bri_lds_spinor<NV, S, T>(bs + (xl + 1 + dx) * SSW, v, f);
-        bri_spin<T>(a, b * T(dx), b * T(dy), b * T(dz), b * T(dt), dx, dy, dz, dt, f, sf);
-        // phase 0: chi(x) (x) conj(S_d psi(x + d)); phase 1: psi(x) (x) conj(S_{-d} chi(x + d))
-        if (phase == 0) bri_outer<T>(ox, sf, gm);
-        else bri_outer<T>(op, sf, gm);
-        // the lane's own slots of the row's sums: written in phase 0, added to in phase 1
-        T* mine = red + ((dx + 1) * R + xl) * 18 * NV + v;
-#pragma unroll
-        for (int e = 0; e < 9; ++e) {
-          if (phase == 0) {
-            mine[(2 * e) * NV] = gm[e / 3][e % 3].r;
-            mine[(2 * e + 1) * NV] = gm[e / 3][e % 3].i;
-          } else {
-            mine[(2 * e) * NV] += gm[e / 3][e % 3].r;
-            mine[(2 * e + 1) * NV] += gm[e / 3][e % 3].i;
-          }
-        }
-      }
-    }
-    __syncthreads();
-    // sums over the N_v lanes of each (direction, site, element), in lane order
-    const int k0 = r == kWgFirstRow ? 2 : 0;
-    const int nout = (3 - k0) * c.n * 9;
-    for (int o = tid; o < nout; o += nth) {
-      const int k = k0 + o / (c.n * 9), rem = o - (k - k0) * c.n * 9;
-      const int site = rem / 9, e = rem - site * 9;
-      const T* src = red + ((k * R + site) * 18 + 2 * e) * NV;
-      T re = T(0), im = T(0);
-#pragma unroll
-      for (int l = 0; l < NV; ++l) {
-        re += src[l];
-        im += src[NV + l];
-      }
-      const int slot = bri_code(k - 1, dy, dz, dt) - 41;
-      S::template store<T>(GW + (size_t(c.row_base + c.x0 + site) * 40 + slot) * 9 + e, mk(re, im));
-    }
-  }
-}
-
-template <int NV, class S, class T>
-static hipError_t brillouin_wgrad_rows_t(const Geom& g, int R, int bt, bool xcd, const void* chi, const void* psi,
-                                         void* GW, hipStream_t st) {
-  using W = typename S::word;
-  const RowTraversal tr = make_row_traversal(g, uint32_t(R), uint32_t(bt));
-  const ChunkTiles o = bri_tiles(g, R, 12L * NV * long(sizeof(W)), false);
-  const dim3 block(NV, R), grid(tr.rows_plane * uint32_t(g.n[2]) * uint32_t(g.n[3]));
-  const size_t lds = size_t(R + 2) * SiteStride<NV, S>::WORDS * sizeof(W) + size_t(3 * R) * 18 * NV * sizeof(T);
-  hipLaunchKernelGGL((bri_wgrad_rows_kernel<NV, S, T>), grid, block, lds, st, g, tr, o, int(xcd), (const W*)chi,
-                     (const W*)psi, (W*)GW);
   return hipGetLastError();
 }
 
@@ -581,28 +392,6 @@ hipError_t launch_brillouin_fly(bool adj, int dtype, const Geom& g, const void* 
     case 24: return brillouin_rows_t<24, C64, float, false>(adj, g, R, bt, xcd, V, in, out, nullptr, mass, st);
   }
   return brillouin_rows_t<12, C64, float>(adj, g, R, bt, xcd, V, in, out, clover, mass, st);
-}
-
-// Row-staged gradient with respect to W (FP32 storage, N_v = 4, 8, 12, 16,
-// 24, the chunks of brillouin_rows_sites); hipErrorNotSupported otherwise (the
-// caller then uses the per-direction kernel).  DSLASH_ROWS=0 disables it.
-hipError_t launch_brillouin_wgrad_rows(int dtype, const Geom& g, const void* chi, const void* psi, void* GW,
-                                       hipStream_t st) {
-  if (knobs().rows.get(1) == 0) return hipErrorNotSupported;
-  if (!aligned16(chi) || !aligned16(psi) || !aligned16(GW)) return hipErrorNotSupported;
-  if (dtype != DT_C64) return hipErrorNotSupported;
-  const int R = brillouin_rows_sites(dtype, g);
-  if (R == 0) return hipErrorNotSupported;
-  int bt = 2;
-  bt = knobs().tband.get(bt);
-  const bool xcd = knobs().xcd.get(1) != 0;
-  switch (g.nv) {
-    case 4: return brillouin_wgrad_rows_t<4, C64, float>(g, R, bt, xcd, chi, psi, GW, st);
-    case 8: return brillouin_wgrad_rows_t<8, C64, float>(g, R, bt, xcd, chi, psi, GW, st);
-    case 16: return brillouin_wgrad_rows_t<16, C64, float>(g, R, bt, xcd, chi, psi, GW, st);
-    case 24: return brillouin_wgrad_rows_t<24, C64, float>(g, R, bt, xcd, chi, psi, GW, st);
-  }
-  return brillouin_wgrad_rows_t<12, C64, float>(g, R, bt, xcd, chi, psi, GW, st);
 }
 
 }  // namespace dsl

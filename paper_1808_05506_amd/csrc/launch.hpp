@@ -98,6 +98,10 @@ hipError_t launch_apply(int op, bool adjoint, int dtype, const Geom& g, const vo
 hipError_t launch_wilson_rows(bool adjoint, int dtype, const Geom& g, const void* U, const void* in, void* out,
                               double mass, hipStream_t st, const void* clover = nullptr, bool compressed = false,
                               int epi = 0, EpiArgs* ea = nullptr);
+// Gradient of D_B with respect to W for C64 and C128 at any N_v
+// (brillouin_wgrad.hip); hipErrorNotSupported otherwise.
+hipError_t launch_brillouin_wgrad_flat(int dtype, const Geom& g, const void* chi, const void* psi, void* GW,
+                                       hipStream_t st);
 // Compute units of the current device (cached per device).
 inline int device_cus() {
   static int cus[64] = {0};
@@ -136,8 +140,6 @@ hipError_t launch_brillouin_fly(bool adjoint, int dtype, const Geom& g, const vo
 hipError_t launch_clover_field(int dtype, const Geom& g, const void* V, void* C, double c_sw, hipStream_t st);
 hipError_t launch_brillouin_wgrad(int dtype, const Geom& g, const void* chi, const void* psi, void* GW,
                                   hipStream_t st);
-hipError_t launch_brillouin_wgrad_rows(int dtype, const Geom& g, const void* chi, const void* psi, void* GW,
-                                       hipStream_t st);
 // W (nullable): the stored off-axis links of V; with it the adjoint uses the
 // path averages of W instead of walking every ordering through V
 hipError_t launch_brillouin_links_backward(int dtype, const Geom& g, const void* V, const void* W, const void* GW,

@@ -7,7 +7,7 @@ FP64 oracle, with the tolerances of the other operator tests."""
 import pytest
 
 import synthetic
-from oracle import brillouin, clover, compress, evenodd, staggered, wilson
+from oracle import brillouin, clover, compress, evenodd, grad, staggered, wilson
 from tests.gpu_util import compare, down, rounded, say, set_knob, up
 
 pytestmark = pytest.mark.gpu
@@ -170,3 +170,18 @@ def test_staggered_flat(dims, dt, nvs, monkeypatch):
                     f"D_S nv={nv} adj={adj}")
         compare(down(D.apply_compressed("staggered", VC, P, 0.1)), compress.apply("staggered", vc, p, 0.1, False), dt,
                 f"D_S compressed nv={nv}")
+
+
+# blocks of every width (several of them at N_v = 26), planes smaller than a chunk,
+# wraps in every direction within a chunk, columns past N_v
+@pytest.mark.parametrize("dt,nvs", [("c64", [1, 2, 3, 4, 5, 6, 8, 9, 10, 12, 16, 24, 26]), ("c128", [1, 4, 5, 7, 8, 10, 12, 13])])
+@pytest.mark.parametrize("dims", [(7, 5, 3, 4), (24, 2, 2, 3), (2, 9, 3, 2)])
+def test_brillouin_wgrad_flat(dims, dt, nvs, monkeypatch):
+    set_knob(monkeypatch, "DSLASH_BRI_LANES", "0")  # small lattices would take the direct kernel
+    W = up(brillouin.build(synthetic.gauge_links(dims, "haar", 880)), dt)
+    for nv in nvs:
+        say(f"case brillouin W gradient flat {dims} nv={nv} {dt}")
+        chi = rounded(synthetic.wilson_spinor(dims, nv, 881 + nv), dt)
+        psi = rounded(synthetic.wilson_spinor(dims, nv, 981 + nv), dt)
+        gW, _ = D.backward("brillouin", W, up(chi, dt), up(psi, dt), 0.1, need_grad_in=False)
+        compare(down(gW), grad.link_grad_brillouin_W(chi, psi), dt, f"G_W nv={nv}")
