@@ -661,6 +661,20 @@ hipError_t launch_cg_update_ep(int dtype, void* e, void* p, const void* r, const
   }
 }
 
+// Scalars of column v: alpha from pq (mode 0), beta, rr and the active flag from
+// rr_new (mode 1).
+__device__ __forceinline__ void cg_scalars(int mode, int v, const CgScalars& c) {
+  const bool on = c.active[v] != 0.0;
+  if (mode == 0) {
+    c.alpha[v] = (on && c.pq[v] > 0.0) ? c.rr[v] / c.pq[v] : 0.0;
+  } else {
+    c.beta[v] = (on && c.rr[v] > 0.0) ? c.rr_new[v] / c.rr[v] : 0.0;
+    if (on) c.rr[v] = c.rr_new[v];
+    const bool still = on && c.rr0[v] > 0.0 && sqrt(c.rr[v] / c.rr0[v]) > c.tol;
+    c.active[v] = still ? 1.0 : 0.0;
+  }
+}
+
 // fold[b][v] = sum of partial[i][v] over the rows i of chunk b (chunks of
 // ceil(nb / kReduceBlocks) consecutive rows), in a fixed order: thread (v, y)
 // adds rows y, y + ry, ... of the chunk, then a fixed LDS tree over y.
@@ -676,18 +690,44 @@ __global__ void __launch_bounds__(256) fold_rows_kernel(const double* __restrict
   if (threadIdx.y == 0 && v < nv) fold[size_t(blockIdx.x) * nv + v] = tot;
 }
 
-hipError_t launch_finish_sum(const double* partial, int nb, int nv, double* out, double* fold, hipStream_t st) {
-  if (nb > 2 * kReduceBlocks && fold) {
-    const ColShape c = col_shape(nv);
-    const size_t lds = size_t(c.block.x) * c.block.y * sizeof(double);
+// Column v's partial sums added up, then its scalars of the CG step (cg_scalars):
+// one workgroup per column.  What bounds it: latency, a launch each (4.8 us and the
+// gap behind it); summing and scalars apart were three launches, twice an iteration.
+constexpr int kStepThreads = 1024;
+__global__ void __launch_bounds__(kStepThreads)
+    cg_step_kernel(int mode, const double* __restrict__ partial, int nb, int nv, CgScalars c) {
+  __shared__ double sh[kStepThreads / 64];
+  const int v = blockIdx.x, tid = int(threadIdx.x);
+  double s = 0.0;
+  for (int b = tid; b < nb; b += kStepThreads) s += partial[size_t(b) * nv + v];
+#pragma unroll
+  for (int w = 32; w > 0; w >>= 1) s += __shfl_xor(s, w);
+  if (tid % 64 == 0) sh[tid / 64] = s;
+  __syncthreads();
+  if (tid == 0) {
+    s = 0.0;
+    for (int w = 0; w < kStepThreads / 64; ++w) s += sh[w];
+    (mode == 0 ? c.pq : c.rr_new)[v] = s;
+    cg_scalars(mode, v, c);
+  }
+}
+
+// More rows than this are folded to kReduceBlocks first.
+constexpr int kStepRows = 16 * kStepThreads;
+
+hipError_t launch_cg_step(int mode, const double* partial, int nb, int nv, const CgScalars& c, double* fold,
+                          hipStream_t st) {
+  if (nb > kStepRows) {
+    const ColShape k = col_shape(nv);
+    const size_t lds = size_t(k.block.x) * k.block.y * sizeof(double);
     const int chunk = (nb + kReduceBlocks - 1) / kReduceBlocks;
-    hipLaunchKernelGGL(fold_rows_kernel, c.grid, c.block, lds, st, partial, nb, nv, chunk, fold);
-    hipError_t e = hipGetLastError();
+    hipLaunchKernelGGL(fold_rows_kernel, k.grid, k.block, lds, st, partial, nb, nv, chunk, fold);
+    const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     partial = fold;
     nb = kReduceBlocks;
   }
-  hipLaunchKernelGGL(finish_sum_kernel, dim3(nv), dim3(256), 0, st, partial, nb, nv, out);
+  hipLaunchKernelGGL(cg_step_kernel, dim3(nv), dim3(kStepThreads), 0, st, mode, partial, nb, nv, c);
   return hipGetLastError();
 }
 
@@ -703,25 +743,12 @@ hipError_t launch_zero(int dtype, void* x, size_t n, hipStream_t st) {
   return hipGetLastError();
 }
 
-__global__ void cg_scalars_kernel(int mode, int nv, double* rr, double* rr_new, double* pq, double* rr0,
-                                  double* alpha, double* beta, double* active, double tol) {
-  for (int v = threadIdx.x; v < nv; v += blockDim.x) {
-    const bool on = active[v] != 0.0;
-    if (mode == 0) {
-      alpha[v] = (on && pq[v] > 0.0) ? rr[v] / pq[v] : 0.0;
-    } else {
-      beta[v] = (on && rr[v] > 0.0) ? rr_new[v] / rr[v] : 0.0;
-      if (on) rr[v] = rr_new[v];
-      const bool still = on && rr0[v] > 0.0 && sqrt(rr[v] / rr0[v]) > tol;
-      active[v] = still ? 1.0 : 0.0;
-    }
-  }
+__global__ void cg_scalars_kernel(int mode, int nv, CgScalars c) {
+  for (int v = threadIdx.x; v < nv; v += blockDim.x) cg_scalars(mode, v, c);
 }
 
-hipError_t launch_cg_scalars(int mode, int nv, double* rr, double* rr_new, double* pq, double* rr0, double* alpha,
-                             double* beta, double* active, double tol, hipStream_t st) {
-  hipLaunchKernelGGL(cg_scalars_kernel, dim3(1), dim3(256), 0, st, mode, nv, rr, rr_new, pq, rr0, alpha, beta,
-                     active, tol);
+hipError_t launch_cg_scalars(int mode, int nv, const CgScalars& c, hipStream_t st) {
+  hipLaunchKernelGGL(cg_scalars_kernel, dim3(1), dim3(256), 0, st, mode, nv, c);
   return hipGetLastError();
 }
 

@@ -200,9 +200,16 @@ hipError_t launch_cg_update_r(int dtype, void* r, const void* s, const double* a
 // e += alpha[v] p;  p = r + beta[v] p
 hipError_t launch_cg_update_ep(int dtype, void* e, void* p, const void* r, const double* alpha, const double* beta,
                                size_t sites, int comps, int nv, hipStream_t st);
-// out[v] = sum over b < nb of partial[b][v], in a fixed order (many rows are
-// first folded to kReduceBlocks rows in fold, kReduceBlocks x nv doubles)
-hipError_t launch_finish_sum(const double* partial, int nb, int nv, double* out, double* fold, hipStream_t st);
+// The per-column values of a CG step on the device (see solver.cpp).
+struct CgScalars {
+  double *rr, *rr_new, *pq, *rr0, *alpha, *beta, *active;
+  double tol;
+};
+// Sums over b < nb of partial[b][v], in a fixed order, into pq (mode 0) or rr_new
+// (mode 1), then launch_cg_scalars of that mode (very many rows are first folded to
+// kReduceBlocks rows in fold, kReduceBlocks x nv doubles).
+hipError_t launch_cg_step(int mode, const double* partial, int nb, int nv, const CgScalars& c, double* fold,
+                          hipStream_t st);
 // p = r + beta[v] p
 hipError_t launch_cg_update_p(int dtype, void* p, const void* r, const double* beta, size_t sites, int comps,
                               int nv, hipStream_t st);
@@ -212,7 +219,6 @@ hipError_t launch_zero(int dtype, void* x, size_t n, hipStream_t st);
 //   mode 0: alpha = active ? rr / pq : 0
 //   mode 1: beta = active ? rr_new / rr : 0; rr = active ? rr_new : rr;
 //           active &= sqrt(rr / rr0) > tol
-hipError_t launch_cg_scalars(int mode, int nv, double* rr, double* rr_new, double* pq, double* rr0, double* alpha,
-                             double* beta, double* active, double tol, hipStream_t st);
+hipError_t launch_cg_scalars(int mode, int nv, const CgScalars& c, hipStream_t st);
 
 }  // namespace dsl

@@ -193,6 +193,7 @@ int solve(const SolveArgs& a) {
   double *rr = sc, *rr_new = sc + nv, *pq = sc + 2 * nv, *rr0 = sc + 3 * nv, *alpha = sc + 4 * nv,
          *beta = sc + 5 * nv, *active = sc + 6 * nv, *nb2 = sc + 7 * nv, *nr2 = sc + 8 * nv,
          *scale = sc + 9 * nv, *inv = sc + 10 * nv;
+  const CgScalars cg{rr, rr_new, pq, rr0, alpha, beta, active, a.inner_tol};
   hipStream_t st = a.stream;
   const Geom g = make_geom(a.dims, nv);
   const size_t vol = g.vol;
@@ -257,25 +258,25 @@ int solve(const SolveArgs& a) {
       hipError_t fe = fuse ? launch_wilson_rows(false, lodt, g, u_lo, p, q, a.mass, st, nullptr, false, EPI_NORM, &ea)
                            : hipErrorNotSupported;
       if (fe == hipSuccess) {
-        DSL_TRY(launch_finish_sum(partial, int(ea.blocks), nv, pq, fold, st), "|Dp|^2");
+        DSL_TRY(launch_cg_step(0, partial, int(ea.blocks), nv, cg, fold, st), "|Dp|^2");
       } else if (fe == hipErrorNotSupported) {
         DSL_TRY(launch_apply(a.op, false, lodt, g, u_lo, p, q, a.mass, st), "inner D p");
         DSL_TRY(launch_norm2(lodt, q, vol, comps, nv, partial, pq, st), "|Dp|^2");
+        DSL_TRY(launch_cg_scalars(0, nv, cg, st), "alpha");
       } else {
         return hipfail(fe, "inner D p");
       }
-      DSL_TRY(launch_cg_scalars(0, nv, rr, rr_new, pq, rr0, alpha, beta, active, a.inner_tol, st), "alpha");
       fe = fuse ? launch_wilson_rows(true, lodt, g, u_lo, q, r, a.mass, st, nullptr, false, EPI_AXPY, &ea)
                 : hipErrorNotSupported;
       if (fe == hipSuccess) {
-        DSL_TRY(launch_finish_sum(partial, int(ea.blocks), nv, rr_new, fold, st), "|r|^2");
+        DSL_TRY(launch_cg_step(1, partial, int(ea.blocks), nv, cg, fold, st), "|r|^2");
       } else if (fe == hipErrorNotSupported) {
         DSL_TRY(launch_apply(a.op, true, lodt, g, u_lo, q, s, a.mass, st), "inner D^dag q");
         DSL_TRY(launch_cg_update_r(lodt, r, s, alpha, vol, comps, nv, partial, rr_new, st), "r update");
+        DSL_TRY(launch_cg_scalars(1, nv, cg, st), "beta");
       } else {
         return hipfail(fe, "inner D^dag q");
       }
-      DSL_TRY(launch_cg_scalars(1, nv, rr, rr_new, pq, rr0, alpha, beta, active, a.inner_tol, st), "beta");
       DSL_TRY(launch_cg_update_ep(lodt, e, p, r, alpha, beta, vol, comps, nv, st), "e and p update");
       for (int v = 0; v < nv; ++v) h.inner[v] += hact[v] != 0.0;
       DSL_TRY(hipMemcpyAsync(hact, active, nv * sizeof(double), hipMemcpyDeviceToHost, st), "copy active");
@@ -313,6 +314,7 @@ static int solve_eo(const SolveArgs& a) {
   double *rr = sc, *rr_new = sc + nv, *pq = sc + 2 * nv, *rr0 = sc + 3 * nv, *alpha = sc + 4 * nv,
          *beta = sc + 5 * nv, *active = sc + 6 * nv, *nb2 = sc + 7 * nv, *nr2 = sc + 8 * nv,
          *scale = sc + 9 * nv, *inv = sc + 10 * nv;
+  const CgScalars cg{rr, rr_new, pq, rr0, alpha, beta, active, a.inner_tol};
   hipStream_t st = a.stream;
   const Geom g = make_geom(a.dims, nv);
   const EoGeom eg = make_eo_geom(a.dims, nv);
@@ -389,26 +391,26 @@ static int solve_eo(const SolveArgs& a) {
                                                   EPI_NORM, &ea)
                            : hipErrorNotSupported;
       if (fe == hipSuccess) {
-        DSL_TRY(launch_finish_sum(partial, int(ea.blocks), nv, pq, fold, st), "|Mp|^2");
+        DSL_TRY(launch_cg_step(0, partial, int(ea.blocks), nv, cg, fold, st), "|Mp|^2");
       } else if (fe == hipErrorNotSupported) {
         DSL_TRY(launch_wilson_eo_hop(false, lodt, eg, 0, u_even, u_odd, tmp, q, p, A, -1.0 / A, st), "inner M p");
         DSL_TRY(launch_norm2(lodt, q, hvol, comps, nv, partial, pq, st), "|Mp|^2");
+        DSL_TRY(launch_cg_scalars(0, nv, cg, st), "alpha");
       } else {
         return hipfail(fe, "inner M p");
       }
-      DSL_TRY(launch_cg_scalars(0, nv, rr, rr_new, pq, rr0, alpha, beta, active, a.inner_tol, st), "alpha");
       DSL_TRY(launch_wilson_eo_hop(true, lodt, eg, 1, u_odd, u_even, q, tmp, nullptr, 0.0, 1.0, st), "inner M^dag q");
       fe = fuse ? launch_wilson_eo_hop(true, lodt, eg, 0, u_even, u_odd, tmp, r, q, A, -1.0 / A, st, EPI_AXPY, &ea)
                 : hipErrorNotSupported;
       if (fe == hipSuccess) {
-        DSL_TRY(launch_finish_sum(partial, int(ea.blocks), nv, rr_new, fold, st), "|r|^2");
+        DSL_TRY(launch_cg_step(1, partial, int(ea.blocks), nv, cg, fold, st), "|r|^2");
       } else if (fe == hipErrorNotSupported) {
         DSL_TRY(launch_wilson_eo_hop(true, lodt, eg, 0, u_even, u_odd, tmp, s, q, A, -1.0 / A, st), "inner M^dag q");
         DSL_TRY(launch_cg_update_r(lodt, r, s, alpha, hvol, comps, nv, partial, rr_new, st), "r update");
+        DSL_TRY(launch_cg_scalars(1, nv, cg, st), "beta");
       } else {
         return hipfail(fe, "inner M^dag q");
       }
-      DSL_TRY(launch_cg_scalars(1, nv, rr, rr_new, pq, rr0, alpha, beta, active, a.inner_tol, st), "beta");
       DSL_TRY(launch_cg_update_ep(lodt, e, p, r, alpha, beta, hvol, comps, nv, st), "e and p update");
       for (int v = 0; v < nv; ++v) h.inner[v] += hact[v] != 0.0;
       DSL_TRY(hipMemcpyAsync(hact, active, nv * sizeof(double), hipMemcpyDeviceToHost, st), "copy active");
