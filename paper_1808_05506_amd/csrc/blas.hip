@@ -672,6 +672,7 @@ __device__ __forceinline__ void cg_scalars(int mode, int v, const CgScalars& c) 
     if (on) c.rr[v] = c.rr_new[v];
     const bool still = on && c.rr0[v] > 0.0 && sqrt(c.rr[v] / c.rr0[v]) > c.tol;
     c.active[v] = still ? 1.0 : 0.0;
+    if (c.flags) c.flags[v] = still ? 1.0 : 0.0;
   }
 }
 

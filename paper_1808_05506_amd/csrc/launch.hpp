@@ -204,6 +204,7 @@ hipError_t launch_cg_update_ep(int dtype, void* e, void* p, const void* r, const
 struct CgScalars {
   double *rr, *rr_new, *pq, *rr0, *alpha, *beta, *active;
   double tol;
+  double* flags;  // mode 1: active again, in memory the host reads; or null
 };
 // Sums over b < nb of partial[b][v], in a fixed order, into pq (mode 0) or rr_new
 // (mode 1), then launch_cg_scalars of that mode (very many rows are first folded to
