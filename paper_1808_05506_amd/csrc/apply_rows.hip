@@ -46,14 +46,16 @@ static bool rows_shape(const Geom& g, int dtype, int pp, bool any_nv, bool knob_
     while (rmax > 1 && march_lds(rmax, nv, wb, pp, 4) > 76 * 1024) --rmax;
     if (uint32_t(rmax) > plane) rmax = int(plane);
     R = rmax;
-    double cost = 0;
-    for (int r = rmax; r >= 1 && 2 * r >= rmax; --r) {
-      if (!halo_fits(r, nv, wb, 4)) break;
-      const double lanes = double((plane + uint32_t(r) - 1) / uint32_t(r)) * ((r * nv + 63) / 64) * 64;
-      if (cost == 0 || lanes < 0.97 * cost) {
+    uint64_t cost = 0;
+    for (uint32_t k = (plane + uint32_t(rmax) - 1) / uint32_t(rmax);; ++k) {  // chunks per plane
+      const int r = int((plane + k - 1) / k);
+      if (2 * r < rmax || !halo_fits(r, nv, wb, 4)) break;
+      const uint64_t lanes = uint64_t(k) * uint32_t((r * nv + 63) / 64);
+      if (cost == 0 || 100 * lanes < 97 * cost) {
         cost = lanes;
         R = r;
       }
+      if (r == 1) break;
     }
   }
   return R >= 1 && R * nv <= 256 && R * nv >= 64 && halo_fits(R, nv, wb, 4);

@@ -598,13 +598,13 @@ hipError_t launch_staggered_rows(bool adj, int dtype, const Geom& g, const void*
   // row's halo (2 sites of 3 N_v words); a row's backward links (9 n words)
   // take ceil(9 / N_v) words a thread
   if (R < 6 || R * nv > 256 || R * nv < 64) return hipErrorNotSupported;
-  // rows of whole chunks with few idle lanes; the others are faster in flat order
-  // (N_v = 12, C64: 24^3 x 48, 144 of 192 lanes, 208 us against 195; 34^4 488
-  // against 403; 32^4, all lanes, 284 against 300.  N_v = 4, 8, where a site's runs
-  // are short: 28^4, N_v = 8, 112 of 128 lanes, 132 against 142; 20^4, N_v = 4 FP64,
-  // 80 of 128 lanes, 45 against 51)
+  // rows that leave few lanes idle; the others are faster in flat order (N_v = 12,
+  // C64: 24^3 x 48, 75 % of the lanes, 208 us against 195; 34^4, 71 %, 488 against
+  // 403; 32^4, all, 284 against 300.  N_v = 4, 8, where a site's runs are short:
+  // 28^4, N_v = 8, 88 %, 132 against 142; 20^4, N_v = 4 FP64, 63 %, 45 against 51)
   const bool asked = knobs().rows.get(1) == 2 || knobs().row_sites.set || knobs().row_depth.set || knobs().tsteps.set;
-  if (!asked && (g.n[0] % R != 0 || 10 * R * nv < (nv <= 8 ? 6 : 9) * ((R * nv + 63) / 64) * 64)) return hipErrorNotSupported;
+  const int lanes = (g.n[0] + R - 1) / R * ((R * nv + 63) / 64) * 64;
+  if (!asked && 10 * g.n[0] * nv < (nv <= 8 ? 6 : 9) * lanes) return hipErrorNotSupported;
   int bt = 4;
   bt = knobs().tband.get(bt);
   bool xcd = true;

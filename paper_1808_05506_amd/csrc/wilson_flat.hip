@@ -23,13 +23,14 @@ FlatShape flat_shape(const Geom& g, int comps, int word_bytes, int vw, int lw, b
   if (pmax > plane) pmax = plane;
   if (pmax < 1) pmax = 1;
   uint32_t best = pmax;
-  double cost = 0;
-  for (uint32_t p = pmax; p >= 1 && 2 * p >= pmax; --p) {
-    const double lanes = double((plane + p - 1) / p) * ((p * gb + 63) / 64) * 64;
-    if (cost == 0 || lanes < 0.9 * cost) {
+  uint64_t cost = 0;
+  for (uint32_t k = (plane + pmax - 1) / pmax, p; 2 * (p = (plane + k - 1) / k) >= pmax; ++k) {
+    const uint64_t lanes = uint64_t(k) * ((p * gb + 63) / 64);
+    if (cost == 0 || 10 * lanes < 9 * cost) {
       cost = lanes;
       best = p;
     }
+    if (p == 1) break;
   }
   s.o.P = best;
   s.o.chunks = (plane + best - 1) / best;
