@@ -95,6 +95,18 @@ static int march_tsteps(const Geom& g, int R, int hn, int pp, int dtype) {
   return int(T);
 }
 
+// Small lattices of 16-bit storage are faster by the direct kernel, which has more
+// lanes in flight: below `lanes` (site, column) pairs, unless a tuning variable or
+// a fused epilogue asks for the rows.  D_W, us by rows and directly: N_v = 4, 110k
+// pairs 14.3 and 7.9 (262k 15.0 against 33 before); N_v = 24, 6k 6.6 and 5.4.
+// Compressed links, 49k: 7.2 and 6.4.  Even-odd hop: F16 N_v = 4, 55k 9.4 and 7.9; C64
+// N_v = 12, 25k 7.2 and 6.6.
+static bool rows_too_small(const Geom& g, size_t lanes, int epi) {
+  const Knobs& k = knobs();
+  const bool asked = k.rows.get(1) == 2 || k.row_sites.set || k.row_depth.set || k.tsteps.set || k.march_pp.set;
+  return !asked && epi == EPI_STORE && size_t(g.vol) * size_t(g.nv) < size_t(k.flat_lanes.get(int(lanes * 1024)));
+}
+
 static hipError_t rows_launch(int dtype, bool any_nv, const RowsCall& c) {
   if (any_nv) return wilson_rows_c64_any(c);
   switch (dtype) {
@@ -121,6 +133,7 @@ hipError_t launch_wilson_eo_rows(bool adj, int dtype, const EoGeom& e, int parit
   if (nv != 4 && nv != 8 && nv != 12 && nv != 16 && nv != 24) return hipErrorNotSupported;
   const int pdims[4] = {e.nh, e.n[1], e.n[2], e.n[3]};
   const Geom g = make_geom(pdims, nv);
+  if (rows_too_small(g, dtype == DT_C64 ? 32 : nv == 4 ? 96 : 64, epi)) return hipErrorNotSupported;
   RowsCall c{};
   if (!rows_shape(g, dtype, 0, false, false, c.R, c.hn, c.late)) return hipErrorNotSupported;
   c.eo = true;
@@ -167,6 +180,7 @@ hipError_t launch_wilson_rows(bool adj, int dtype, const Geom& g, const void* U,
   const bool any_nv = nv != 4 && nv != 8 && nv != 12 && nv != 16 && nv != 24;
   if (any_nv && (dtype != DT_C64 || nv < 2 || nv > 23)) return hipErrorNotSupported;
   if (nv != 12 && (clover || compressed || epi != EPI_STORE)) return hipErrorNotSupported;
+  if (rows_too_small(g, compressed ? 128 : dtype == DT_C64 ? 1 : nv == 4 ? 128 : 16, epi)) return hipErrorNotSupported;
   // N_v = 12 with the clover term or a tuning variable set: hn = 4
   const bool knob_form =
       nv == 12 && (clover || knobs().tsteps.set || knobs().march_pp.set || (knobs().row_depth.set && epi == EPI_STORE));

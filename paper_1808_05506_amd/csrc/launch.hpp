@@ -24,7 +24,7 @@ struct Knob {
 struct Knobs {
   Knob sites_per_block, tband, xcd, row_sites, row_depth, tsteps, march_pp, rows, row_lds_extra, cg_fuse;
   Knob grad_tile_y, grad_tile_z, march_tile_y, march_tile_z, bri_tile_y, bri_tile_z, rows_tile_y,
-      rows_tile_z, blas_nt, wmarch_tile_y, wmarch_tile_z, flat_zb, flat_kb, bri_lanes;
+      rows_tile_z, blas_nt, wmarch_tile_y, wmarch_tile_z, flat_zb, flat_kb, flat_lanes, bri_lanes;
 };
 inline Knob read_knob(const char* name) {
   Knob k;
@@ -59,6 +59,7 @@ inline Knobs read_knobs() {
   r.wmarch_tile_z = read_knob("DSLASH_WMARCH_TILE_Z");
   r.flat_zb = read_knob("DSLASH_FLAT_ZB");
   r.flat_kb = read_knob("DSLASH_FLAT_KB");
+  r.flat_lanes = read_knob("DSLASH_FLAT_LANES");
   r.bri_lanes = read_knob("DSLASH_BRI_LANES");
   return r;
 }
@@ -120,13 +121,13 @@ inline int device_cus() {
 hipError_t launch_brillouin_flat(bool adjoint, int dtype, const Geom& g, const void* Wl, const void* in, void* out,
                                  double mass, hipStream_t st, const void* clover);
 // D_W at any N_v, storage and alignment by the flat kernel (wilson_flat.hpp);
-// hipErrorNotSupported where a plane of sites reaches 4 GB, or for an epilogue
-// that does not fit.
+// hipErrorNotSupported where a plane of sites reaches 4 GB, for an epilogue that
+// does not fit, and where the direct kernel is the faster one.
 hipError_t launch_wilson_flat(bool adjoint, int dtype, const Geom& g, const void* U, const void* in, void* out,
                               double mass, hipStream_t st, const void* clover, bool compressed, int epi = 0,
                               EpiArgs* ea = nullptr);
 // D_S at any N_v, storage and alignment (staggered_flat.hip); hipErrorNotSupported
-// where a plane of sites reaches 4 GB.
+// where a plane of sites reaches 4 GB and where the direct kernel is the faster one.
 hipError_t launch_staggered_flat(bool adjoint, int dtype, const Geom& g, const void* U, const void* in, void* out,
                                  double mass, hipStream_t st, bool compressed);
 hipError_t launch_staggered_rows(bool adjoint, int dtype, const Geom& g, const void* U, const void* in, void* out,

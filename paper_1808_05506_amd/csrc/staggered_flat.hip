@@ -224,6 +224,13 @@ hipError_t launch_staggered_flat(bool adj, int dtype, const Geom& g, const void*
                                  double mass, hipStream_t st, bool compressed) {
   if (!flat_covers(g, dtype)) return hipErrorNotSupported;
   const int vw = flat_vw(dtype, g.nv, aligned16(in) && aligned16(out));
+  // Small lattices go to the direct kernel, which has a lane for every column.
+  // Fewest lanes for this one, us here and there: FP64 any from N_v = 4 on (8^4, N_v =
+  // 4 5.8 and 6.2), 256k below (N_v = 1, 65k 26.3 and 18.9); else 80k (C64 N_v = 4, 55k
+  // 7.4 and 6.2, N_v = 1, 65k 9.9 and 9.4; BF16 N_v = 4, 65k 10.3 and 6.4, N_v = 6, 83k 7.0
+  // and 7.6; four columns 128k: F16 N_v = 12, 83k 9.9 and 8.7, 196k 14.9 and 15.3).
+  const uint32_t fewest = dtype == DT_C128 ? (g.nv < 4 ? 256 : 0) : vw == 4 ? 128 : 80;
+  if (size_t(g.vol) * size_t(g.nv / vw) < size_t(knobs().flat_lanes.get(int(fewest * 1024)))) return hipErrorNotSupported;
   const StagCall a{adj, compressed, &g, U, in, out, mass, st};
   switch (dtype) {
     case DT_BF16: return stag_flat16<BF16>(vw, a);

@@ -603,6 +603,11 @@ hipError_t launch_staggered_rows(bool adj, int dtype, const Geom& g, const void*
   // 403; 32^4, all, 284 against 300.  N_v = 4, 8, where a site's runs are short:
   // 28^4, N_v = 8, 88 %, 132 against 142; 20^4, N_v = 4 FP64, 63 %, 45 against 51)
   const bool asked = knobs().rows.get(1) == 2 || knobs().row_sites.set || knobs().row_depth.set || knobs().tsteps.set;
+  // and lattices that fill the chip with marching workgroups: below that the rows
+  // take 20 us and more (C64: 8^4, N_v = 12, 18.7 us, directly 3.7; 16^4, N_v = 12, 25.0 and
+  // 18.7 in flat order; 16^3 x 32, N_v = 12, inputs from HBM 39.4 and 43.0.  FP64: 16^4,
+  // N_v = 4, 24.0 and 19.4; 16^3 x 32 28.1 and 35.3)
+  if (!asked && g.vol < 131072u) return hipErrorNotSupported;
   const int lanes = (g.n[0] + R - 1) / R * ((R * nv + 63) / 64) * 64;
   if (!asked && 10 * g.n[0] * nv < (nv <= 8 ? 6 : 9) * lanes) return hipErrorNotSupported;
   int bt = 4;

@@ -64,11 +64,22 @@ FlatShape flat_shape(const Geom& g, int comps, int word_bytes, int vw, int lw, b
 hipError_t launch_wilson_flat(bool adj, int dtype, const Geom& g, const void* U, const void* in, void* out, double mass,
                               hipStream_t st, const void* clover, bool compressed, int epi, EpiArgs* ea) {
   if (!flat_covers(g, dtype)) return hipErrorNotSupported;
-  const bool one_word = dtype != DT_C128 && flat_vw(dtype, g.nv, aligned16(in) && aligned16(out)) == 1;
+  const int vw = flat_vw(dtype, g.nv, aligned16(in) && aligned16(out));
+  const bool one_word = dtype != DT_C128 && vw == 1;
   if (!clover && epi == EPI_STORE && (g.nv == 1 || (one_word && (compressed || g.nv < 6)))) return hipErrorNotSupported;
+  // Small lattices: several columns a lane and chunks of up to 256 lanes leave the
+  // chip idle that the direct kernel fills.  Fewest lanes for this one, us here
+  // and there: FP64 144k (N_v = 4, 110k 27.8 and 20.9; N_v = 12, 172k 30.0 and 30.3); two
+  // columns 64k (BF16 N_v = 2, 27k 16.6 and 10.2, N_v = 6, 83k 16.2 and 20.7), with the
+  // clover term 128k (C64 N_v = 4, 55k 22.8 and 18.1, 131k 42.4 and 45.3); compressed
+  // or four columns 256k (C64 N_v = 4, 131k 30.1 and 26.9; F16 N_v = 4 with the clover
+  // term, 65k 42.4 and 21.8).  One FP32 column a lane: any (N_v = 5 with the
+  // clover term, 8^4 8.5 and 9.9).
+  const uint32_t fewest = dtype == DT_C128 ? 144 : one_word ? 0 : (compressed || vw == 4) ? 256 : clover ? 128 : 64;
+  if (epi == EPI_STORE && size_t(g.vol) * size_t(g.nv / vw) < size_t(knobs().flat_lanes.get(int(fewest * 1024))))
+    return hipErrorNotSupported;
   EpiArgs none;
   EpiArgs& e = ea ? *ea : none;
-  const int vw = flat_vw(dtype, g.nv, aligned16(in) && aligned16(out));
   const FlatArgs a{U, U, in, in, clover, out, 4.0 + mass, -0.5, 0};
   if (dtype == DT_BF16 || dtype == DT_F16) return launch_wilson_flat16(dtype, vw, adj, g, a, compressed, epi, st, e);
   return flat_forms_wide<false>(dtype, vw, adj, g, a, compressed, epi, st, e);

@@ -19,6 +19,12 @@ if not torch.cuda.is_available():
 from paper_1808_05506_amd import dslash as D  # noqa: E402
 
 
+@pytest.fixture(autouse=True)
+def _small_lattices_too(monkeypatch):
+    # lattices of a test's size would take the direct kernels
+    set_knob(monkeypatch, "DSLASH_FLAT_LANES", "0")
+
+
 def _fields(dims, nv, dt, seed):
     u = rounded(synthetic.gauge_links(dims, "haar", seed), dt)
     p = rounded(synthetic.wilson_spinor(dims, nv, seed + 1), dt)
