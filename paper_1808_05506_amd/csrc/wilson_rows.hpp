@@ -1401,16 +1401,18 @@ inline FlatMarch one_row_order(const Geom& g, int R, long site_bytes) {
   FlatMarch m = make_flat_march(g, uint32_t(R), 1u);
   double best = -1;
   uint32_t kb = 1, zb = 1;
-  for (uint32_t z = 1; z <= uint32_t(g.n[2]); ++z)
-    for (uint32_t k = 1; k <= m.chunks; ++k) {
-      if (z * k > 1 && double(z) * k * R * site_bytes > 1280.0 * 1024) break;
-      const double s = (k < m.chunks ? 2.0 * g.n[0] / (double(k) * R) : 0.0) + (z < uint32_t(g.n[2]) ? 2.0 / z : 0.0);
-      if (best < 0 || s < best) {
-        best = s;
-        kb = k;
-        zb = z;
-      }
+  for (uint32_t z = 1; z <= uint32_t(g.n[2]); ++z) {
+    uint32_t k = uint32_t(1280L * 1024 / (long(z) * R * site_bytes));  // the most chunks have the smallest surface
+    if (k > m.chunks) k = m.chunks;
+    if (k < 1 && z > 1) break;
+    if (k < 1) k = 1;
+    const double s = (k < m.chunks ? 2.0 * g.n[0] / (double(k) * R) : 0.0) + (z < uint32_t(g.n[2]) ? 2.0 / z : 0.0);
+    if (best < 0 || s < best) {
+      best = s;
+      kb = k;
+      zb = z;
     }
+  }
   m.kb = kb;
   m.zb = zb;
   if (knobs().rows_tile_y.set || knobs().rows_tile_z.set)
