@@ -605,9 +605,9 @@ hipError_t launch_staggered_rows(bool adj, int dtype, const Geom& g, const void*
   const bool asked = knobs().rows.get(1) == 2 || knobs().row_sites.set || knobs().row_depth.set || knobs().tsteps.set;
   // and lattices that fill the chip with marching workgroups: below that the rows
   // take 20 us and more (C64: 8^4, N_v = 12, 18.7 us, directly 3.7; 16^4, N_v = 12, 25.0 and
-  // 18.7 in flat order; 16^3 x 32, N_v = 12, inputs from HBM 39.4 and 43.0.  FP64: 16^4,
-  // N_v = 4, 24.0 and 19.4; 16^3 x 32 28.1 and 35.3)
-  if (!asked && g.vol < 131072u) return hipErrorNotSupported;
+  // 18.6 in flat order; 16^2 x 20 x 24, 38.0 and 38.6; 16^3 x 32 39.4 and 43.0.  FP64:
+  // 16^4, N_v = 4, 24.0 and 18.9, N_v = 24 56.8 and 62.8; 16x20x18x18, N_v = 12 52.0 and 56.3)
+  if (!asked && g.vol < (dtype == DT_C64 ? 131072u : nv == 24 ? 65536u : 98304u)) return hipErrorNotSupported;
   const int lanes = (g.n[0] + R - 1) / R * ((R * nv + 63) / 64) * 64;
   if (!asked && 10 * g.n[0] * nv < (nv <= 8 ? 6 : 9) * lanes) return hipErrorNotSupported;
   int bt = 4;
