@@ -66,7 +66,15 @@ hipError_t launch_wilson_flat(bool adj, int dtype, const Geom& g, const void* U,
   if (!flat_covers(g, dtype)) return hipErrorNotSupported;
   const int vw = flat_vw(dtype, g.nv, aligned16(in) && aligned16(out));
   const bool one_word = dtype != DT_C128 && vw == 1;
-  if (!clover && epi == EPI_STORE && (g.nv == 1 || (one_word && (compressed || g.nv < 6)))) return hipErrorNotSupported;
+  if (epi == EPI_STORE && (g.nv == 1 || (!clover && one_word && (compressed || g.nv < 6)))) return hipErrorNotSupported;
+  // Few columns a site with the clover term or compressed links (21x16x17x33, us here
+  // and directly): C64 clover N_v = 2 171 and 128, compressed N_v = 4 106 and 85, N_v = 8 148
+  // and 161; BF16 clover N_v = 2 102 and 63, N_v = 8 138 and 102, N_v = 16 209 and 206 (F16
+  // 216 and 293), compressed N_v = 8 103 and 90, N_v = 16 170 and 198.
+  if (epi == EPI_STORE && !knobs().flat_lanes.set &&
+      ((clover && g.nv <= 2) || ((clover || compressed) && vw == 4 && g.nv < 16) ||
+       (compressed && dtype == DT_C64 && g.nv < 8)))
+    return hipErrorNotSupported;
   // Small lattices: several columns a lane and chunks of up to 256 lanes leave the
   // chip idle that the direct kernel fills.  Fewest lanes for this one, us here
   // and there: FP64 144k (N_v = 4, 110k 27.8 and 20.9; N_v = 12, 172k 30.0 and 30.3); two
