@@ -97,9 +97,9 @@ __global__ void __launch_bounds__(256, 4)
   }
   {
     // A thread moves one word (link mu, element) of every nth / 4 LW-th site, four
-    // or eight (one FP32 column a lane: 32^4, N_v = 1 154 us against 186) sites in flight;
+    // or eight (at most 8 bytes a lane: 32^4, C64 N_v = 1 154 us against 186) sites in flight;
     // sites past the end repeat the last one.
-    constexpr int SWL = 4 * LW, F = VW == 1 && sizeof(W) == 8 ? 8 : 4;
+    constexpr int SWL = 4 * LW, F = VW * int(sizeof(W)) <= 8 ? 8 : 4;
     const int per = nth / SWL, k0 = tid / SWL, e = tid - k0 * SWL, mu = e / LW;
     if (nth < SWL) {
       for (int q = tid; q < n * SWL; q += nth) {
