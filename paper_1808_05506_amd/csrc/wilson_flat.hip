@@ -1,60 +1,8 @@
-// Flat D_W kernels on the full lattice (see wilson_flat.hpp): the launch shape
-// and the C64 and C128 forms.
+// Flat D_W kernels on the full lattice (see wilson_flat.hpp): the dispatch and the
+// C64 and C128 forms.
 #include "wilson_flat.hpp"
 
 namespace dsl {
-
-// P: at most 256 lanes and 80 KB of links (two workgroups a CU), and of those
-// the one that wastes the fewest lanes on the chunk count and the last wave.
-// zb x kb: whole planes whose spinors at one t take at most 1.2 MB where two fit,
-// else three planes of about a third of 1.05 MB each.  FP64 takes two workgroups
-// a CU (79 KB of LDS asked for): more of them in flight than that push each
-// other's neighbour rows out of the L2.  FP64, N_v = 12, 24^3 x 48: 1141 us with
-// 3 planes x 7 of 28 chunks at two workgroups a CU, 1167 at three, 1368 with four
-// and the tile of the smallest surface; 16^3 x 32: 220 us with 2 whole planes, 230
-// with 4 planes x 7 of 13 chunks, 242 and 272 as before.
-FlatShape flat_shape(const Geom& g, int comps, int word_bytes, int vw, int lw, bool clover) {
-  FlatShape s{};
-  const uint32_t plane = uint32_t(g.n[0]) * uint32_t(g.n[1]);
-  const uint32_t groups = uint32_t(g.nv / vw), gb = groups < 256 ? groups : 256;
-  const size_t site_lds = size_t(8 * lw + (clover ? 36 : 0)) * word_bytes;
-  uint32_t pmax = 256 / gb;
-  if (pmax > 80 * 1024 / site_lds) pmax = uint32_t(80 * 1024 / site_lds);
-  if (pmax > plane) pmax = plane;
-  if (pmax < 1) pmax = 1;
-  uint32_t best = pmax;
-  uint64_t cost = 0;
-  for (uint32_t k = (plane + pmax - 1) / pmax, p; 2 * (p = (plane + k - 1) / k) >= pmax; ++k) {
-    const uint64_t lanes = uint64_t(k) * ((p * gb + 63) / 64);
-    if (cost == 0 || 10 * lanes < 9 * cost) {
-      cost = lanes;
-      best = p;
-    }
-    if (p == 1) break;
-  }
-  s.o.P = best;
-  s.o.chunks = (plane + best - 1) / best;
-  s.o.groups = FastDiv::make(gb);
-  const double row = double(comps) * g.nv * word_bytes * best, full = row * s.o.chunks;
-  if (full <= 0.6 * 1024 * 1024) {
-    s.o.kb = s.o.chunks;
-    s.o.zb = uint32_t(1.2 * 1024 * 1024 / full);
-    if (s.o.zb > uint32_t(g.n[2])) s.o.zb = uint32_t(g.n[2]);
-  } else {
-    s.o.zb = g.n[2] < 3 ? uint32_t(g.n[2]) : 3u;
-    s.o.kb = uint32_t(1.05 * 1024 * 1024 / (s.o.zb * row));
-    if (s.o.kb < 1) s.o.kb = 1;
-    if (s.o.kb > s.o.chunks) s.o.kb = s.o.chunks;
-  }
-  if (knobs().flat_zb.set) s.o.zb = uint32_t(knobs().flat_zb.value);
-  if (knobs().flat_kb.set) s.o.kb = uint32_t(knobs().flat_kb.value);
-  s.grid = dim3(s.o.chunks * uint32_t(g.n[2]) * uint32_t(g.n[3]), (groups + gb - 1) / gb);
-  s.block = dim3(best * gb);
-  s.lds = size_t(best) * site_lds;
-  if (comps == 12 && word_bytes == 16 && s.lds < 79 * 1024) s.lds = 79 * 1024;
-  if (s.lds < size_t(knobs().row_lds_extra.get(0))) s.lds = size_t(knobs().row_lds_extra.get(0));
-  return s;
-}
 
 // Left to the direct kernel, which is faster there: N_v = 1 (16^3 x 32 C64 26.6
 // against 66.4 us, its site is one contiguous run), and lanes of one 8- or 4-byte

@@ -21,17 +21,10 @@
 // before, with links and spinors loaded by each lane in (site, column) order).
 #pragma once
 
-#include "launch.hpp"
+#include "flat_order.hpp"
 #include "stencils.hpp"
 
 namespace dsl {
-
-// Workgroup order (see above): zb planes x kb chunks per tile.
-struct FlatOrder {
-  uint32_t P, chunks;  // sites per chunk, chunks per plane
-  uint32_t zb, kb;
-  FastDiv groups;      // lanes per site in a workgroup
-};
 
 template <int BYTES> struct FlatPiece;
 template <> struct FlatPiece<16> { typedef u32x4 type; };
@@ -145,33 +138,6 @@ __device__ __forceinline__ void flat_half(const typename FlatVec<S, VW>::V (&raw
       else if constexpr (MU == 2) acc[k][3][a] -= ci<C>(r);
       else acc[k][2 + s][a] += cs<C>(r);
     }
-}
-
-struct FlatSite {
-  uint32_t p0, n;  // first in-plane site of the chunk, its live sites
-  int z, t;
-};
-
-DSL_HD FlatSite flat_site(const Geom& g, const FlatOrder& o, uint32_t L) {
-  const uint32_t nz = uint32_t(g.n[2]), nt = uint32_t(g.n[3]), nk = o.chunks;
-  const uint32_t slab = nk * o.zb * nt;  // zb planes: all chunks and t
-  const uint32_t sz = L / slab;
-  L -= sz * slab;
-  const uint32_t z0 = sz * o.zb, zw = nz - z0 < o.zb ? nz - z0 : o.zb;
-  const uint32_t tile = o.kb * zw * nt;
-  const uint32_t sk = L / tile;
-  L -= sk * tile;
-  const uint32_t k0 = sk * o.kb, kw = nk - k0 < o.kb ? nk - k0 : o.kb;
-  const uint32_t per_t = kw * zw, t = L / per_t;
-  L -= t * per_t;
-  const uint32_t zz = L / kw, k = k0 + (L - zz * kw);
-  const uint32_t plane = uint32_t(g.n[0]) * uint32_t(g.n[1]);
-  FlatSite s;
-  s.p0 = k * o.P;
-  s.n = plane - s.p0 < o.P ? plane - s.p0 : o.P;
-  s.z = int(z0 + zz);
-  s.t = int(t);
-  return s;
 }
 
 // Rows of six pieces in flight and waves per SIMD: three halves in flight with
@@ -406,28 +372,6 @@ __global__ void __launch_bounds__(256, (FlatDepth<S, VW>::waves))
       }
     }
   }
-}
-
-// Launch shape, chosen by flat_shape (wilson_flat.hip).
-struct FlatShape {
-  FlatOrder o;
-  dim3 grid, block;
-  size_t lds;
-};
-// comps: spinor components of a site (12, D_S 3).
-FlatShape flat_shape(const Geom& g, int comps, int word_bytes, int vw, int lw, bool clover);
-
-// Columns per lane: as many as 16 bytes hold and N_v is a multiple of; one for
-// fields off a 16-byte boundary.
-inline int flat_vw(int dtype, int nv, bool aligned) {
-  int vw = dtype == DT_C128 || !aligned ? 1 : (dtype == DT_C64 ? 2 : 4);
-  while (nv % vw) vw /= 2;
-  return vw;
-}
-
-// The lanes address a plane of sites by 32-bit byte offsets.
-inline bool flat_covers(const Geom& g, int dtype) {
-  return uint64_t(g.n[0]) * uint64_t(g.n[1]) * 12u * uint64_t(g.nv) * dtype_bytes(dtype) < (1ull << 32);
 }
 
 struct FlatArgs {

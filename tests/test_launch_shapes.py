@@ -1,0 +1,107 @@
+"""Launch shapes and workgroup orders of the kernels, on the host: the headers that
+hold them are compiled into a small library without device code."""
+import ctypes
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+HIPCC = "/opt/rocm/bin/hipcc" if os.path.exists("/opt/rocm/bin/hipcc") else shutil.which("hipcc")
+
+pytestmark = pytest.mark.skipif(HIPCC is None, reason="no hipcc")
+
+SOURCE = r"""
+#include "flat_order.hpp"
+#include <vector>
+using namespace dsl;
+
+static Geom geom(const int* d, int nv) {
+  Geom g{};
+  for (int i = 0; i < 4; ++i) g.n[i] = d[i];
+  g.stride[0] = 1;
+  for (int i = 1; i < 4; ++i) g.stride[i] = g.stride[i - 1] * d[i - 1];
+  g.vol = uint32_t(d[0]) * d[1] * d[2] * d[3];
+  g.nv = nv;
+  g.dx = FastDiv::make(d[0]);
+  g.dy = FastDiv::make(d[1]);
+  g.dz = FastDiv::make(d[2]);
+  return g;
+}
+
+extern "C" {
+void reload() { knob_store() = read_knobs(); }
+
+// out: P, chunks, zb, kb, grid x, grid y, block
+void flat(const int* d, int nv, int comps, int wb, int vw, long long* out) {
+  const FlatShape s = flat_shape(geom(d, nv), comps, wb, vw, 9, false);
+  const long long v[] = {s.o.P, s.o.chunks, s.o.zb, s.o.kb, s.grid.x, s.grid.y, s.block.x};
+  for (int i = 0; i < 7; ++i) out[i] = v[i];
+}
+
+// how many (chunk, z, t) the order with these tiles does not visit exactly once
+int flat_missed(const int* d, int nv, int comps, int wb, int vw) {
+  const Geom g = geom(d, nv);
+  const FlatShape s = flat_shape(g, comps, wb, vw, 9, false);
+  std::vector<int> seen(size_t(s.o.chunks) * d[2] * d[3], 0);
+  int bad = 0;
+  for (uint32_t L = 0; L < s.grid.x; ++L) {
+    const FlatSite f = flat_site(g, s.o, L);
+    const long plane = long(d[0]) * d[1];
+    if (f.p0 % s.o.P || long(f.p0) >= plane || f.z < 0 || f.z >= d[2] || f.t < 0 || f.t >= d[3] || f.n < 1 ||
+        long(f.p0) + f.n > plane) {
+      ++bad;
+      continue;
+    }
+    ++seen[(size_t(f.t) * d[2] + f.z) * s.o.chunks + f.p0 / s.o.P];
+  }
+  for (int n : seen) bad += n != 1;
+  return bad;
+}
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def shapes(tmp_path_factory):
+    d = tmp_path_factory.mktemp("shapes")
+    src, lib = d / "shapes.cpp", d / "shapes.so"
+    src.write_text(SOURCE)
+    csrc = os.path.join(ROOT, "paper_1808_05506_amd", "csrc")
+    subprocess.run([HIPCC, "-x", "hip", "--cuda-host-only", "-O1", "-std=c++17", "-fPIC", "-shared", "-I", csrc,
+                    str(src), "-o", str(lib)], check=True, capture_output=True, timeout=300)
+    return ctypes.CDLL(str(lib))
+
+
+def _dims(d):
+    return (ctypes.c_int * 4)(*d)
+
+
+def _flat(lib, dims, nv, comps, wb, vw):
+    out = (ctypes.c_longlong * 7)()
+    lib.flat(_dims(dims), nv, comps, wb, vw, out)
+    return dict(zip(("P", "chunks", "zb", "kb", "gx", "gy", "block"), out))
+
+
+@pytest.fixture
+def knob(shapes, monkeypatch):
+    def set_(**kw):
+        for k, v in kw.items():
+            monkeypatch.setenv(k, v)
+        shapes.reload()
+    yield set_
+    monkeypatch.undo()
+    shapes.reload()
+
+
+# unset, the whole range (0, text that is no number, negative, too large) and tiles
+# that divide nothing: the tile is never empty, and every chunk is visited once
+@pytest.mark.parametrize("zb", [None, "0", "-1", "none", "2", "2147483647", "-2147483648"])
+@pytest.mark.parametrize("kb", [None, "0", "-3", "3", "2147483647"])
+def test_flat_tiles_are_never_empty(shapes, knob, zb, kb):
+    knob(**{k: v for k, v in (("DSLASH_FLAT_ZB", zb), ("DSLASH_FLAT_KB", kb)) if v is not None})
+    for dims, nv, comps, wb, vw in [((9, 30, 5, 3), 12, 12, 16, 1), ((4, 4, 4, 4), 4, 3, 8, 2), ((34, 34, 3, 2), 6, 12, 4, 2)]:
+        s = _flat(shapes, dims, nv, comps, wb, vw)
+        assert 1 <= s["zb"] <= dims[2] and 1 <= s["kb"] <= s["chunks"], (s, dims)
+        assert shapes.flat_missed(_dims(dims), nv, comps, wb, vw) == 0, (s, dims)
