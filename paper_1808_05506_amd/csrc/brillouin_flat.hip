@@ -326,6 +326,7 @@ hipError_t bri_flat_t(const BriCall& a) {
   pick_tile(g, long(g.n[0]) * 12 * B::NB * long(sizeof(W)), 1280L * 1024, by, bz);
   flat_march_tile(g, m, knobs().bri_tile_y.get(by), knobs().bri_tile_z.get(bz));
   const dim3 grid(m.grid, uint32_t((g.nv + B::NB - 1) / B::NB));
+  if (!grid_fits(grid, dim3(B::LANES))) return hipErrorNotSupported;
   const T diag = T(a.mass) + T(15.0 / 8.0);
   const int xcd = knobs().xcd.get(1) != 0;
 #define DSL_BF(A, CL)                                                                                            \

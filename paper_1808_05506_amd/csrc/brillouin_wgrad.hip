@@ -230,6 +230,7 @@ hipError_t bri_wgrad_t(const GradCall& a) {
   int by, bz;
   pick_tile(g, long(g.n[0]) * 24 * B::NB * long(sizeof(W)), 1280L * 1024, by, bz);
   flat_march_tile(g, m, knobs().bri_tile_y.get(by), knobs().bri_tile_z.get(bz));
+  if (!grid_fits(dim3(m.grid), dim3(B::LANES))) return hipErrorNotSupported;
   hipLaunchKernelGGL((brillouin_wgrad_kernel<B, S, T>), dim3(m.grid), dim3(B::LANES), 0, a.st, g, m,
                      int(knobs().xcd.get(1) != 0), (const W*)a.chi, (const W*)a.psi, (W*)a.GW);
   return hipGetLastError();

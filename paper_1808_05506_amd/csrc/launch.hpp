@@ -82,6 +82,14 @@ inline int links_per_site(int op) { return op == OP_BRILLOUIN ? 40 : 4; }
 
 Geom make_geom(const int dims[4], int nv);
 
+// HIP takes fewer than 2^32 work-items in a dimension of the grid.  The kernels with
+// all their lanes in x ask this before a launch and leave what is larger to the direct
+// kernel, whose columns and sites are in two dimensions (D_S in 16 bits, N_v = 63, 96^3 x
+// 80: 4.5e9 lanes, 117 GB).
+inline bool grid_fits(const dim3& grid, const dim3& block) {
+  return uint64_t(grid.x) * block.x < (1ull << 32) && uint64_t(grid.y) * block.y < (1ull << 32);
+}
+
 // Thread shape of the (site, right-hand side) kernels.
 struct Shape {
   dim3 grid, block;
@@ -121,13 +129,13 @@ inline int device_cus() {
 hipError_t launch_brillouin_flat(bool adjoint, int dtype, const Geom& g, const void* Wl, const void* in, void* out,
                                  double mass, hipStream_t st, const void* clover);
 // D_W at any N_v, storage and alignment by the flat kernel (wilson_flat.hpp);
-// hipErrorNotSupported where a plane of sites reaches 4 GB, for an epilogue that
-// does not fit, and where the direct kernel is the faster one.
+// hipErrorNotSupported where a plane of sites reaches 4 GB or the grid 2^32 lanes, for
+// an epilogue that does not fit, and where the direct kernel is the faster one.
 hipError_t launch_wilson_flat(bool adjoint, int dtype, const Geom& g, const void* U, const void* in, void* out,
                               double mass, hipStream_t st, const void* clover, bool compressed, int epi = 0,
                               EpiArgs* ea = nullptr);
 // D_S at any N_v, storage and alignment (staggered_flat.hip); hipErrorNotSupported
-// where a plane of sites reaches 4 GB and where the direct kernel is the faster one.
+// where a plane of sites reaches 4 GB or the grid 2^32 lanes and where the direct kernel is the faster one.
 hipError_t launch_staggered_flat(bool adjoint, int dtype, const Geom& g, const void* U, const void* in, void* out,
                                  double mass, hipStream_t st, bool compressed);
 hipError_t launch_staggered_rows(bool adjoint, int dtype, const Geom& g, const void* U, const void* in, void* out,

@@ -201,6 +201,7 @@ template <class S, class T, int VW, int NVC = 0>
 hipError_t stag_flat(const StagCall& a) {
   using W = typename S::word;
   const FlatShape s = flat_shape(*a.g, 3, int(sizeof(W)), VW, a.compressed ? 6 : 9, false);
+  if (!grid_fits(s.grid, s.block)) return hipErrorNotSupported;
   const int xcd = knobs().xcd.get(1);
 #define DSL_SK(A, L)                                                                                             \
   hipLaunchKernelGGL((staggered_flat_kernel<A, L, S, T, VW, NVC>), s.grid, s.block, s.lds, a.st, *a.g, s.o, xcd, \

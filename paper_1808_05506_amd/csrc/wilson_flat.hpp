@@ -385,6 +385,7 @@ template <bool EO, bool ADJ, bool CLOV, int LW, int EPI, class S, class T, int V
 static hipError_t flat_launch(const Geom& g, const FlatArgs& a, hipStream_t st, EpiArgs& ea) {
   using W = typename S::word;
   const FlatShape s = flat_shape(g, 12, int(sizeof(W)), VW, LW, CLOV);
+  if (!grid_fits(s.grid, s.block)) return hipErrorNotSupported;
   if (EPI != EPI_STORE) {
     if (s.grid.y > 1 || s.grid.x > ea.capacity) return hipErrorNotSupported;
     ea.blocks = s.grid.x;

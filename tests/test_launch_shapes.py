@@ -1,5 +1,6 @@
-"""Launch shapes and workgroup orders of the kernels, on the host: the headers that
-hold them are compiled into a small library without device code."""
+"""Launch shapes, workgroup orders and dispatch rules of the kernels, on the host: the
+headers that hold them are compiled into a small library without device code, which
+also calls the launchers of libdslash.so where they return before any launch."""
 import ctypes
 import os
 import shutil
@@ -10,7 +11,12 @@ import pytest
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 HIPCC = "/opt/rocm/bin/hipcc" if os.path.exists("/opt/rocm/bin/hipcc") else shutil.which("hipcc")
 
-pytestmark = pytest.mark.skipif(HIPCC is None, reason="no hipcc")
+LIB = os.path.join(ROOT, "paper_1808_05506_amd", "libdslash.so")
+
+pytestmark = pytest.mark.skipif(HIPCC is None or not os.path.exists(LIB), reason="no hipcc or libdslash.so not built")
+
+C64, C128, BF16, F16 = 0, 1, 2, 3
+NOT_SUPPORTED = 801  # hipErrorNotSupported: left to the direct kernel
 
 SOURCE = r"""
 #include "flat_order.hpp"
@@ -59,6 +65,11 @@ int flat_missed(const int* d, int nv, int comps, int wb, int vw) {
   for (int n : seen) bad += n != 1;
   return bad;
 }
+
+// The launchers on null fields, for shapes that they refuse before they launch.
+int launch_staggered(int dtype, const int* d, int nv) {
+  return launch_staggered_flat(false, dtype, geom(d, nv), nullptr, nullptr, nullptr, 0.1, nullptr, false);
+}
 }
 """
 
@@ -70,7 +81,8 @@ def shapes(tmp_path_factory):
     src.write_text(SOURCE)
     csrc = os.path.join(ROOT, "paper_1808_05506_amd", "csrc")
     subprocess.run([HIPCC, "-x", "hip", "--cuda-host-only", "-O1", "-std=c++17", "-fPIC", "-shared", "-I", csrc,
-                    str(src), "-o", str(lib)], check=True, capture_output=True, timeout=300)
+                    str(src), "-x", "none", LIB, "-Wl,-rpath," + os.path.dirname(LIB), "-o", str(lib)],
+                   check=True, capture_output=True, timeout=300)
     return ctypes.CDLL(str(lib))
 
 
@@ -105,3 +117,13 @@ def test_flat_tiles_are_never_empty(shapes, knob, zb, kb):
         s = _flat(shapes, dims, nv, comps, wb, vw)
         assert 1 <= s["zb"] <= dims[2] and 1 <= s["kb"] <= s["chunks"], (s, dims)
         assert shapes.flat_missed(_dims(dims), nv, comps, wb, vw) == 0, (s, dims)
+
+
+# (site, column) lanes past HIP's 2^32 work-items per grid dimension go to the direct
+# kernel, which spreads them over two dimensions
+@pytest.mark.skipif(os.path.exists("/dev/kfd"), reason="host only: a shape not refused would be launched")
+@pytest.mark.parametrize("dtype,dims,nv", [(BF16, (96, 96, 96, 80), 63), (F16, (64, 64, 64, 64), 514), (C64, (64, 64, 64, 64), 257)])
+def test_flat_grids_past_the_launch_limit_are_refused(shapes, dtype, dims, nv):
+    vol = dims[0] * dims[1] * dims[2] * dims[3]
+    assert vol * nv // (2 if nv % 2 == 0 else 1) >= 2 ** 32
+    assert shapes.launch_staggered(dtype, _dims(dims), nv) == NOT_SUPPORTED
