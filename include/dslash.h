@@ -283,7 +283,9 @@ size_t dslash_solve_workspace_bytes(const int dims[4], int Nc, int Nv, int inner
  * C128 device array holding the initial guess on entry and the solution on
  * exit.  workspace: device memory of at least dslash_solve_workspace_bytes
  * bytes, owned by the caller.  x may not overlap b, U64, U_lo or the
- * workspace (E_ALIAS).
+ * workspace (E_ALIAS).  For the call the solve also holds Nv doubles of pinned
+ * host memory and an event, made on the stream's device; where they cannot be
+ * had it copies the Nv flags of an iteration instead.
  * final_relres (host, Nv doubles, nullable): true FP64 relative residuals.
  * iters (host, 2 * Nv ints, nullable): iters[v] = inner iterations run on
  * column v, iters[Nv + v] = outer corrections applied to column v.

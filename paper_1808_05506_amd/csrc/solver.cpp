@@ -24,6 +24,7 @@
 #include <vector>
 
 #include "../../include/dslash.h"
+#include "flag_poll.hpp"
 #include "launch.hpp"
 
 namespace dsl {
@@ -170,54 +171,6 @@ struct HostBufs {
 };
 }  // namespace
 
-namespace {
-// The active flags of a CG iteration in host memory that the device writes
-// (CgScalars::flags): the host reads them while the iteration's last pass runs, and
-// the next iteration is queued before that pass ends.  Allocated per solve; not used
-// (host == nullptr) where the solve may not allocate or the allocation fails: the
-// flags are then copied behind the last pass, and the device idles from its end until
-// the host has seen them.
-struct FlagPoll {
-  double* host = nullptr;
-  hipEvent_t ev = nullptr;
-  FlagPoll(int nv, bool may_allocate) {
-    if (!may_allocate) return;
-    void* p = nullptr;
-    if (hipHostMalloc(&p, size_t(nv) * sizeof(double), hipHostMallocDefault) != hipSuccess) {
-      (void)hipGetLastError();
-      return;
-    }
-    if (hipEventCreateWithFlags(&ev, hipEventDisableTiming) != hipSuccess) {
-      (void)hipGetLastError();
-      (void)hipHostFree(p);
-      return;
-    }
-    host = static_cast<double*>(p);
-  }
-  ~FlagPoll() {
-    if (!host) return;
-    (void)hipEventSynchronize(ev);
-    (void)hipEventDestroy(ev);
-    (void)hipHostFree(host);
-  }
-  FlagPoll(const FlagPoll&) = delete;
-  FlagPoll& operator=(const FlagPoll&) = delete;
-  // after the launch that writes the flags
-  hipError_t mark(hipStream_t st) { return host ? hipEventRecord(ev, st) : hipSuccess; }
-  // the flags in hact
-  hipError_t read(const double* active, double* hact, int nv, hipStream_t st) {
-    if (host) {
-      const hipError_t e = hipEventSynchronize(ev);
-      if (e != hipSuccess) return e;
-      for (int v = 0; v < nv; ++v) hact[v] = host[v];
-      return hipSuccess;
-    }
-    const hipError_t e = hipMemcpyAsync(hact, active, nv * sizeof(double), hipMemcpyDeviceToHost, st);
-    return e != hipSuccess ? e : hipStreamSynchronize(st);
-  }
-};
-}  // namespace
-
 static int solve_eo(const SolveArgs& a);
 
 int solve(const SolveArgs& a) {
@@ -241,7 +194,7 @@ int solve(const SolveArgs& a) {
   double *rr = sc, *rr_new = sc + nv, *pq = sc + 2 * nv, *rr0 = sc + 3 * nv, *alpha = sc + 4 * nv,
          *beta = sc + 5 * nv, *active = sc + 6 * nv, *nb2 = sc + 7 * nv, *nr2 = sc + 8 * nv,
          *scale = sc + 9 * nv, *inv = sc + 10 * nv;
-  FlagPoll poll(nv, a.host_d == nullptr);
+  FlagPoll poll(nv, a.host_d == nullptr, a.stream);
   const CgScalars cg{rr, rr_new, pq, rr0, alpha, beta, active, a.inner_tol, poll.host};
   hipStream_t st = a.stream;
   const Geom g = make_geom(a.dims, nv);
@@ -326,10 +279,10 @@ int solve(const SolveArgs& a) {
       } else {
         return hipfail(fe, "inner D^dag q");
       }
-      DSL_TRY(poll.mark(st), "flags");
+      poll.mark();
       DSL_TRY(launch_cg_update_ep(lodt, e, p, r, alpha, beta, vol, comps, nv, st), "e and p update");
       for (int v = 0; v < nv; ++v) h.inner[v] += hact[v] != 0.0;
-      DSL_TRY(poll.read(active, hact, nv, st), "active flags");
+      DSL_TRY(poll.read(active, hact, nv), "active flags");
       bool any = false;
       for (int v = 0; v < nv; ++v) any = any || hact[v] != 0.0;
       if (!any) break;
@@ -363,7 +316,7 @@ static int solve_eo(const SolveArgs& a) {
   double *rr = sc, *rr_new = sc + nv, *pq = sc + 2 * nv, *rr0 = sc + 3 * nv, *alpha = sc + 4 * nv,
          *beta = sc + 5 * nv, *active = sc + 6 * nv, *nb2 = sc + 7 * nv, *nr2 = sc + 8 * nv,
          *scale = sc + 9 * nv, *inv = sc + 10 * nv;
-  FlagPoll poll(nv, a.host_d == nullptr);
+  FlagPoll poll(nv, a.host_d == nullptr, a.stream);
   const CgScalars cg{rr, rr_new, pq, rr0, alpha, beta, active, a.inner_tol, poll.host};
   hipStream_t st = a.stream;
   const Geom g = make_geom(a.dims, nv);
@@ -461,10 +414,10 @@ static int solve_eo(const SolveArgs& a) {
       } else {
         return hipfail(fe, "inner M^dag q");
       }
-      DSL_TRY(poll.mark(st), "flags");
+      poll.mark();
       DSL_TRY(launch_cg_update_ep(lodt, e, p, r, alpha, beta, hvol, comps, nv, st), "e and p update");
       for (int v = 0; v < nv; ++v) h.inner[v] += hact[v] != 0.0;
-      DSL_TRY(poll.read(active, hact, nv, st), "active flags");
+      DSL_TRY(poll.read(active, hact, nv), "active flags");
       bool any = false;
       for (int v = 0; v < nv; ++v) any = any || hact[v] != 0.0;
       if (!any) break;
