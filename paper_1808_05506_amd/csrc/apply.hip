@@ -159,10 +159,10 @@ static hipError_t apply_op(bool adj, int dtype, const Geom& g, const void* U, co
   return hipErrorInvalidValue;
 }
 
-// DSLASH_ROWS: 0 the direct kernels only, 1 (default) the row-staged kernel
-// where it covers the configuration and the direct one elsewhere, 2 the
-// row-staged kernel or hipErrorNotSupported (to test that a configuration
-// takes it).
+// DSLASH_ROWS: 0 the direct kernels only; 1 (default) the row-staged kernel where it
+// covers the configuration, else the flat one (D_S, D_W), else the direct one; 2 the
+// row-staged kernel (D_B: the flat one) or hipErrorNotSupported (to test that a
+// configuration takes it).
 hipError_t launch_apply(int op, bool adj, int dtype, const Geom& g, const void* U, const void* in, void* out,
                         double mass, hipStream_t st, const void* clover, bool compressed) {
   const bool rows_only = knobs().rows.get(1) == 2;

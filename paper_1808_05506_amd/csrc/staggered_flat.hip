@@ -224,7 +224,7 @@ hipError_t stag_flat16(int vw, const StagCall& a) {
 
 hipError_t launch_staggered_flat(bool adj, int dtype, const Geom& g, const void* U, const void* in, void* out,
                                  double mass, hipStream_t st, bool compressed) {
-  if (!flat_covers(g, dtype)) return hipErrorNotSupported;
+  if (knobs().rows.get(1) == 0 || !flat_covers(g, dtype)) return hipErrorNotSupported;
   const int vw = flat_vw(dtype, g.nv, aligned16(in) && aligned16(out));
   // Small lattices go to the direct kernel, which has a lane for every column.
   // Fewest lanes for this one, us here and there: FP64 any from N_v = 4 on (8^4, N_v =

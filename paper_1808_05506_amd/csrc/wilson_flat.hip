@@ -11,7 +11,7 @@ namespace dsl {
 // against 68; FP16, N_v = 7: 88.9 against 81.8, so from N_v = 6 on this one).
 hipError_t launch_wilson_flat(bool adj, int dtype, const Geom& g, const void* U, const void* in, void* out, double mass,
                               hipStream_t st, const void* clover, bool compressed, int epi, EpiArgs* ea) {
-  if (!flat_covers(g, dtype)) return hipErrorNotSupported;
+  if (knobs().rows.get(1) == 0 || !flat_covers(g, dtype)) return hipErrorNotSupported;
   const int vw = flat_vw(dtype, g.nv, aligned16(in) && aligned16(out));
   const bool one_word = dtype != DT_C128 && vw == 1;
   if (epi == EPI_STORE && (g.nv == 1 || (!clover && one_word && (compressed || g.nv < 6)))) return hipErrorNotSupported;

@@ -1,0 +1,65 @@
+"""Which kernel family a call takes, and the families that small test lattices reach
+only when a tuning variable asks for them, against the FP64 oracle."""
+import pytest
+
+import synthetic
+from oracle import compress, staggered, wilson
+from tests.gpu_util import compare, down, rounded, say, set_knob, up
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+if not torch.cuda.is_available():
+    pytest.skip("no GPU", allow_module_level=True)
+
+from paper_1808_05506_amd import dslash as D  # noqa: E402
+
+NEVER = "2000000000"  # more lanes than any lattice has: the direct kernel
+
+
+# The direct and the flat kernel add the hops in different orders, so their bits tell
+# which one ran.
+@pytest.mark.parametrize("op,dt,nv", [("wilson", "c128", 12), ("wilson", "c64", 26), ("staggered", "c128", 12),
+                                      ("staggered", "c64", 12), ("staggered", "c128", 7)])
+def test_rows_0_selects_the_direct_kernel(op, dt, nv, monkeypatch):
+    dims = (10, 4, 6, 4)
+    say(f"case direct by DSLASH_ROWS=0 {op} {dt} nv={nv}")
+    gen = synthetic.wilson_spinor if op == "wilson" else synthetic.staggered_spinor
+    u, p = rounded(synthetic.gauge_links(dims, "haar", 900), dt), rounded(gen(dims, nv, 901), dt)
+    U, P = up(u, dt), up(p, dt)
+    set_knob(monkeypatch, "DSLASH_FLAT_LANES", "0")
+    flat = D.apply(op, U, P, 0.1)
+    set_knob(monkeypatch, "DSLASH_FLAT_LANES", NEVER)
+    direct = D.apply(op, U, P, 0.1)
+    set_knob(monkeypatch, "DSLASH_FLAT_LANES", "0")
+    set_knob(monkeypatch, "DSLASH_ROWS", "0")
+    got = D.apply(op, U, P, 0.1)
+    assert not torch.equal(flat, direct)
+    assert torch.equal(got, direct)
+    compare(down(got), (wilson if op == "wilson" else staggered).apply(u, p, 0.1, False), dt, f"{op} direct")
+
+
+# The flat D_S kernel where rows would hold whole chunks as well (these lattices are too
+# small for the row-staged one), at its columns per lane and past one workgroup
+@pytest.mark.parametrize("dt,nvs", [("c64", [1, 2, 5, 8, 12, 13, 24, 300]), ("c128", [1, 3, 12, 24]),
+                                    ("bf16", [1, 2, 4, 6, 12]), ("f16", [3, 4, 10, 12])])
+@pytest.mark.parametrize("dims", [(10, 4, 2, 4), (2, 6, 4, 2), (16, 2, 2, 6), (38, 2, 4, 2)])
+def test_staggered_flat(dims, dt, nvs, monkeypatch):
+    u = rounded(synthetic.gauge_links(dims, "haar", 910), dt)
+    vc = rounded(compress.compress(synthetic.gauge_links(dims, "smooth", 911)), dt)
+    U, VC = up(u, dt), up(vc, dt)
+    for nv in nvs:
+        say(f"case staggered flat {dims} nv={nv} {dt}")
+        p = rounded(synthetic.staggered_spinor(dims, nv, 912 + nv), dt)
+        P = up(p, dt)
+        set_knob(monkeypatch, "DSLASH_FLAT_LANES", NEVER)
+        direct = D.apply("staggered", U, P, 0.1)
+        set_knob(monkeypatch, "DSLASH_FLAT_LANES", "0")
+        differ = False
+        for adj in (False, True):
+            out = D.apply("staggered", U, P, 0.1, adjoint=adj)
+            compare(down(out), staggered.apply(u, p, 0.1, adj), dt, f"D_S nv={nv} adj={adj}")
+            differ = differ or (not adj and not torch.equal(out, direct))
+        assert differ or dt in ("bf16", "f16")  # (16-bit stores round the difference away)
+        compare(down(D.apply_compressed("staggered", VC, P, 0.1)), compress.apply("staggered", vc, p, 0.1, False), dt,
+                f"D_S compressed nv={nv}")

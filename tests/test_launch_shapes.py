@@ -66,7 +66,12 @@ int flat_missed(const int* d, int nv, int comps, int wb, int vw) {
   return bad;
 }
 
-// The launchers on null fields, for shapes that they refuse before they launch.
+// The launchers on null fields, for calls that they refuse before they launch.
+int launch_wilson(int dtype, const int* d, int nv, int clover, int compressed) {
+  static float c;
+  return launch_wilson_flat(false, dtype, geom(d, nv), nullptr, nullptr, nullptr, 0.1, nullptr, clover ? &c : nullptr,
+                            compressed != 0);
+}
 int launch_staggered(int dtype, const int* d, int nv) {
   return launch_staggered_flat(false, dtype, geom(d, nv), nullptr, nullptr, nullptr, 0.1, nullptr, false);
 }
@@ -127,3 +132,19 @@ def test_flat_grids_past_the_launch_limit_are_refused(shapes, dtype, dims, nv):
     vol = dims[0] * dims[1] * dims[2] * dims[3]
     assert vol * nv // (2 if nv % 2 == 0 else 1) >= 2 ** 32
     assert shapes.launch_staggered(dtype, _dims(dims), nv) == NOT_SUPPORTED
+
+
+# DSLASH_ROWS=0: the direct kernels, not the flat ones
+@pytest.mark.skipif(os.path.exists("/dev/kfd"), reason="host only: a call not refused would be launched")
+@pytest.mark.parametrize("dtype,nv", [(C64, 5), (C64, 12), (C64, 26), (C128, 7), (C128, 12), (BF16, 12), (F16, 16)])
+def test_rows_0_leaves_every_call_to_the_direct_kernels(shapes, dtype, nv, monkeypatch):
+    monkeypatch.setenv("DSLASH_ROWS", "0")
+    shapes.dslash_reload_tuning()
+    try:
+        d = _dims((32, 32, 32, 32))
+        assert shapes.launch_staggered(dtype, d, nv) == NOT_SUPPORTED
+        for clover, compressed in [(0, 0), (1, 0), (0, 1)]:
+            assert shapes.launch_wilson(dtype, d, nv, clover, compressed) == NOT_SUPPORTED
+    finally:
+        monkeypatch.undo()
+        shapes.dslash_reload_tuning()
