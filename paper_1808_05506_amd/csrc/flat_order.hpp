@@ -64,12 +64,12 @@ inline bool flat_covers(const Geom& g, int dtype) {
 // P: at most 256 lanes and 80 KB of links (two workgroups a CU), and of those
 // the one that wastes the fewest lanes on the chunk count and the last wave.
 // zb x kb: whole planes whose spinors at one t take at most 1.2 MB where two fit,
-// else three planes of about a third of 1.05 MB each.  FP64 takes two workgroups
-// a CU (79 KB of LDS asked for): more of them in flight than that push each
-// other's neighbour rows out of the L2.  FP64, N_v = 12, 24^3 x 48: 1141 us with
-// 3 planes x 7 of 28 chunks at two workgroups a CU, 1167 at three, 1368 with four
-// and the tile of the smallest surface; 16^3 x 32: 220 us with 2 whole planes, 230
-// with 4 planes x 7 of 13 chunks, 242 and 272 as before.
+// else three planes of about a third of 1.05 MB each (FP64, N_v = 12, 16^3 x 32: 220 us
+// with 2 whole planes, 230 with 4 planes x 7 of 13 chunks).  D_W in pieces of 16 bytes
+// takes two workgroups a CU (79 KB of LDS asked for): more of them in flight than that
+// push each other's neighbour rows out of the L2.  24^3 x 48, two, three and four a CU:
+// FP64, N_v = 12, 1141, 1167 and 1368 us; C64, N_v = 26, 1287, 1445 and 1590.  With the clover
+// term in C64 three are as good (12^4, N_v = 16: 32 us against 38 at two).
 inline FlatShape flat_shape(const Geom& g, int comps, int word_bytes, int vw, int lw, bool clover) {
   FlatShape s{};
   const uint32_t plane = uint32_t(g.n[0]) * uint32_t(g.n[1]);
@@ -114,7 +114,8 @@ inline FlatShape flat_shape(const Geom& g, int comps, int word_bytes, int vw, in
   s.grid = dim3(s.o.chunks * uint32_t(g.n[2]) * uint32_t(g.n[3]), (groups + gb - 1) / gb);
   s.block = dim3(best * gb);
   s.lds = size_t(best) * site_lds;
-  if (comps == 12 && word_bytes == 16 && s.lds < 79 * 1024) s.lds = 79 * 1024;
+  const bool two = comps == 12 && (word_bytes == 16 || (word_bytes == 8 && vw == 2 && !clover));
+  if (two && s.lds < 79 * 1024) s.lds = 79 * 1024;
   if (s.lds < size_t(knobs().row_lds_extra.get(0))) s.lds = size_t(knobs().row_lds_extra.get(0));
   return s;
 }

@@ -129,11 +129,10 @@ inline int device_cus() {
 hipError_t launch_brillouin_flat(bool adjoint, int dtype, const Geom& g, const void* Wl, const void* in, void* out,
                                  double mass, hipStream_t st, const void* clover);
 // D_W at any N_v, storage and alignment by the flat kernel (wilson_flat.hpp);
-// hipErrorNotSupported where a plane of sites reaches 4 GB or the grid 2^32 lanes, for
-// an epilogue that does not fit, and where the direct kernel is the faster one.
+// hipErrorNotSupported where a plane of sites reaches 4 GB or the grid 2^32 lanes and
+// where the direct kernel is the faster one.
 hipError_t launch_wilson_flat(bool adjoint, int dtype, const Geom& g, const void* U, const void* in, void* out,
-                              double mass, hipStream_t st, const void* clover, bool compressed, int epi = 0,
-                              EpiArgs* ea = nullptr);
+                              double mass, hipStream_t st, const void* clover, bool compressed);
 // D_S at any N_v, storage and alignment (staggered_flat.hip); hipErrorNotSupported
 // where a plane of sites reaches 4 GB or the grid 2^32 lanes and where the direct kernel is the faster one.
 hipError_t launch_staggered_flat(bool adjoint, int dtype, const Geom& g, const void* U, const void* in, void* out,

@@ -1,7 +1,8 @@
-// Flat D_W kernels: any lattice, any N_v, any storage, with the clover term,
-// compressed links and the even-odd hop (wilson_flat.hip, eo.hip instantiate
-// them).  The row-staged kernels (rows.hpp) need x-rows and block sizes that
-// fill their workgroups; these take what is left.
+// Flat D_W kernels: any lattice, any N_v, any storage, also with the clover term or
+// compressed links (wilson_flat.hip, wilson_flat16.hip instantiate them).  The
+// row-staged kernels (wilson_rows.hpp) have FP32 arithmetic and block sizes and
+// chunks that fill their workgroups; these take what is left, but for the calls that
+// the direct kernel is faster at (launch_wilson_flat).
 //
 // A workgroup owns P consecutive sites of an (x, y) plane at one (z, t), across
 // row ends, and all N_v right-hand sides: lane (site, group) holds VW columns,
@@ -17,8 +18,8 @@
 // hits are cheap (30 TB/s measured for these access patterns, 9 TB/s from the
 // Infinity Cache), so the order of the workgroups decides: tiles of planes x
 // chunks, t sweeping inside a tile, each XCD a contiguous eighth of that order
-// (flat_shape).  FP64, N_v = 12, 24^3 x 48: 1141 us, 3.0 TB/s algorithmic (1906
-// before, with links and spinors loaded by each lane in (site, column) order).
+// (flat_shape).  FP64, N_v = 12, 24^3 x 48: 1050 us, 3.3 TB/s algorithmic (1906
+// with links and spinors loaded by each lane in (site, column) order).
 #pragma once
 
 #include "flat_order.hpp"
@@ -140,9 +141,9 @@ __device__ __forceinline__ void flat_half(const typename FlatVec<S, VW>::V (&raw
     }
 }
 
-// Rows of six pieces in flight and waves per SIMD: three halves in flight with
-// 8-byte pieces or a 16-bit format (74 VGPRs at one FP32 column, 6 waves), two
-// at two FP32 columns (128 VGPRs, 4 waves) and for FP64 (114, 4 waves).
+// Half hops in flight and waves per SIMD: three at one column a lane in FP32
+// arithmetic (74 VGPRs, 6 waves), two at more columns (two: 128 VGPRs, 4 waves) and
+// for FP64 (114, 4 waves).
 template <class S, int VW>
 struct FlatDepth {
   static constexpr int LANE = VW * int(sizeof(typename S::real));
@@ -150,18 +151,13 @@ struct FlatDepth {
   static constexpr int waves = VW >= 4 ? 2 : (LANE >= 8 ? 3 : 4);
 };
 
-// out = c_add add + c_hop sum_mu [(1 - gamma_mu) V_mu(x) in(x+mu) + (1 + gamma_mu) V_mu(x-mu)^dag in(x-mu)]
-// (+ C(x) add(x) with the clover term).  Full lattice: Uf = Ub = the links,
-// add = in, c_add = 4 + m0, c_hop = -1/2.  EO: the packed sites of parity p
-// (g: the packed geometry), Uf the links of parity p, Ub those of 1 - p, add
-// may be null; x + 1 sits at packed i + r and x - 1 at i - 1 + r, r = (p + y +
-// z + t) mod 2.
-template <bool EO, bool ADJ, bool CLOV, int LW, int EPI, class S, class T, int VW, int NVC>
+// out = diag in - 1/2 sum_mu [(1 - gamma_mu) V_mu(x) in(x+mu) + (1 + gamma_mu) V_mu(x-mu)^dag in(x-mu)]
+// (+ C(x) in(x) with the clover term), diag = 4 + m0.
+template <bool ADJ, bool CLOV, int LW, class S, class T, int VW, int NVC>
 __global__ void __launch_bounds__(256, (FlatDepth<S, VW>::waves))
-    wilson_flat_kernel(Geom g, FlatOrder o, int xcd, int parity, const typename S::word* __restrict__ Uf,
-                       const typename S::word* __restrict__ Ub, const typename S::word* __restrict__ in,
-                       typename S::word* __restrict__ out, const typename S::word* __restrict__ add,
-                       const typename S::word* __restrict__ Cl, T c_add, T c_hop, EpiArgs ea) {
+    wilson_flat_kernel(Geom g, FlatOrder o, int xcd, const typename S::word* __restrict__ U,
+                       const typename S::word* __restrict__ in, typename S::word* __restrict__ out,
+                       const typename S::word* __restrict__ Cl, T diag) {
   using W = typename S::word;
   using V = typename FlatVec<S, VW>::V;
   constexpr int D = FlatDepth<S, VW>::value;
@@ -183,11 +179,7 @@ __global__ void __launch_bounds__(256, (FlatDepth<S, VW>::waves))
 
   // in-plane index of the x - 1 neighbour of in-plane site p
   auto x_minus = [&](uint32_t p) -> uint32_t {
-    const uint32_t y = g.dx.div(p), x = p - y * Nx;
-    if constexpr (EO) {
-      const uint32_t r = (uint32_t(parity) + y + uint32_t(z) + uint32_t(t)) & 1u;
-      return r ? p : (x == 0 ? p + Nx - 1 : p - 1);
-    }
+    const uint32_t x = p - g.dx.div(p) * Nx;
     return x == 0 ? p + Nx - 1 : p - 1;
   };
 
@@ -200,13 +192,8 @@ __global__ void __launch_bounds__(256, (FlatDepth<S, VW>::waves))
   const int ic = i < n ? i : n - 1;
   gq = gq < G ? gq : G - 1;
   const uint32_t p = fs.p0 + uint32_t(ic);
-  const uint32_t y = g.dx.div(p), x = p - y * Nx;
-  const uint32_t p_xm = x_minus(p);
-  uint32_t p_xp = x + 1 == Nx ? p + 1 - Nx : p + 1;
-  if constexpr (EO) {
-    const uint32_t r = (uint32_t(parity) + y + uint32_t(z) + uint32_t(t)) & 1u;
-    if (!r) p_xp = p;
-  }
+  const uint32_t x = p - g.dx.div(p) * Nx;
+  const uint32_t p_xm = x_minus(p), p_xp = x + 1 == Nx ? p + 1 - Nx : p + 1;
   const uint32_t p_yp = p + Nx < Nxy ? p + Nx : p + Nx - Nxy, p_ym = p >= Nx ? p - Nx : p + Nxy - Nx;
   const uint32_t sb = 12u * uint32_t(nv) * uint32_t(sizeof(W)), vb = uint32_t(gq * VW) * uint32_t(sizeof(W));
   const size_t sw = size_t(12) * size_t(nv);
@@ -240,7 +227,7 @@ __global__ void __launch_bounds__(256, (FlatDepth<S, VW>::waves))
   {
     // four words in flight a thread and pass; indices past the end repeat the last word
     const int words = n * 4 * LW, last = words - 1;
-    const W* const uf = Uf + size_t(plane + fs.p0) * 4 * LW;
+    const W* const uf = U + size_t(plane + fs.p0) * 4 * LW;
 #pragma nounroll
     for (int q0 = tid; q0 < words; q0 += 4 * nth) {
       W a[4], b[4];
@@ -252,7 +239,7 @@ __global__ void __launch_bounds__(256, (FlatDepth<S, VW>::waves))
         const uint32_t sn = mu == 0 ? plane + x_minus(pk)
                                     : mu == 1 ? plane + (pk >= Nx ? pk - Nx : pk + Nxy - Nx) : (mu == 2 ? pl_zm : pl_tm) + pk;
         a[j] = uf[q];
-        b[j] = Ub[size_t(sn) * 4 * LW + e];
+        b[j] = U[size_t(sn) * 4 * LW + e];
       }
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
@@ -287,7 +274,8 @@ __global__ void __launch_bounds__(256, (FlatDepth<S, VW>::waves))
 
   const size_t own = sw * plane;
   char* const op = reinterpret_cast<char*>(out + own) + v_p;
-  const char* const ap = add ? reinterpret_cast<const char*>(add + own) + v_p : nullptr;
+  const char* const ap = reinterpret_cast<const char*>(in_p) + v_p;
+  const T hop = T(-0.5);
   const size_t cb = size_t(nv) * sizeof(W);
   if constexpr (CLOV) {
     cpx<T> q[VW][4][3];
@@ -300,8 +288,8 @@ __global__ void __launch_bounds__(256, (FlatDepth<S, VW>::waves))
 #pragma unroll
         for (int k = 0; k < VW; ++k) {
           q[k][a][b] = f[k];
-          acc[k][a][b].r = fma(c_add, f[k].r, c_hop * acc[k][a][b].r);
-          acc[k][a][b].i = fma(c_add, f[k].i, c_hop * acc[k][a][b].i);
+          acc[k][a][b].r = fma(diag, f[k].r, hop * acc[k][a][b].r);
+          acc[k][a][b].i = fma(diag, f[k].i, hop * acc[k][a][b].i);
         }
       }
 #pragma unroll
@@ -318,137 +306,65 @@ __global__ void __launch_bounds__(256, (FlatDepth<S, VW>::waves))
         }
     }
   } else {
-    T sum[VW], al[VW];
-#pragma unroll
-    for (int k = 0; k < VW; ++k) {
-      sum[k] = T(0);
-      al[k] = EPI == EPI_AXPY ? T(ea.alpha[gq * VW + k]) : T(0);
-    }
 #pragma unroll
     for (int a = 0; a < 4; ++a)
 #pragma unroll
       for (int b = 0; b < 3; ++b) {
         const size_t cbo = size_t(a * 3 + b) * cb;
-        cpx<T> f[VW], r[VW];
+        cpx<T> f[VW];
+        FlatVec<S, VW>::template unpack<T>(*reinterpret_cast<const V*>(ap + cbo), f);
 #pragma unroll
-        for (int k = 0; k < VW; ++k) r[k] = {c_hop * acc[k][a][b].r, c_hop * acc[k][a][b].i};
-        if (ap) {
-          FlatVec<S, VW>::template unpack<T>(*reinterpret_cast<const V*>(ap + cbo), f);
-#pragma unroll
-          for (int k = 0; k < VW; ++k) r[k] = {fma(c_add, f[k].r, r[k].r), fma(c_add, f[k].i, r[k].i)};
-        }
-        V z = FlatVec<S, VW>::template pack<T>(r);
-        if constexpr (EPI == EPI_AXPY) {
-          // r -= alpha (result as stored), the residual rounded as stored
-          cpx<T> w[VW];
-          FlatVec<S, VW>::template unpack<T>(z, w);
-          FlatVec<S, VW>::template unpack<T>(*reinterpret_cast<const V*>(op + cbo), r);
-#pragma unroll
-          for (int k = 0; k < VW; ++k) r[k] = rmadd(r[k], -al[k], w[k]);
-          z = FlatVec<S, VW>::template pack<T>(r);
-        }
-        if (live) *reinterpret_cast<V*>(op + cbo) = z;
-        if constexpr (EPI != EPI_STORE) {
-          cpx<T> w[VW];
-          FlatVec<S, VW>::template unpack<T>(z, w);
-#pragma unroll
-          for (int k = 0; k < VW; ++k) sum[k] = fma(w[k].r, w[k].r, fma(w[k].i, w[k].i, sum[k]));
-        }
+        for (int k = 0; k < VW; ++k)
+          f[k] = {fma(diag, f[k].r, hop * acc[k][a][b].r), fma(diag, f[k].i, hop * acc[k][a][b].i)};
+        if (live) *reinterpret_cast<V*>(op + cbo) = FlatVec<S, VW>::template pack<T>(f);
       }
-    if constexpr (EPI != EPI_STORE) {
-      // per-column sums over the chunk's sites in a fixed order: [P][nv] doubles
-      // in LDS (the links are done with), then thread v adds column v's sites
-      double* const ls = reinterpret_cast<double*>(smem_flat);
-      __syncthreads();
-      if (live) {
-#pragma unroll
-        for (int k = 0; k < VW; ++k) ls[i * nv + gq * VW + k] = double(sum[k]);
-      }
-      __syncthreads();
-      for (int v = tid; v < nv; v += nth) {
-        double s = 0.0;
-        for (int k = 0; k < n; ++k) s += ls[k * nv + v];
-        ea.partial[size_t(blockIdx.x) * nv + v] = s;
-      }
-    }
   }
 }
 
 struct FlatArgs {
-  const void *Uf, *Ub, *in, *add, *clover;
+  const void *U, *in, *clover;
   void* out;
-  double c_add, c_hop;
-  int parity;  // EO only
+  double mass;
 };
 
-template <bool EO, bool ADJ, bool CLOV, int LW, int EPI, class S, class T, int VW, int NVC>
-static hipError_t flat_launch(const Geom& g, const FlatArgs& a, hipStream_t st, EpiArgs& ea) {
+template <bool ADJ, bool CLOV, int LW, class S, class T, int VW, int NVC>
+static hipError_t flat_launch(const Geom& g, const FlatArgs& a, hipStream_t st) {
   using W = typename S::word;
   const FlatShape s = flat_shape(g, 12, int(sizeof(W)), VW, LW, CLOV);
   if (!grid_fits(s.grid, s.block)) return hipErrorNotSupported;
-  if (EPI != EPI_STORE) {
-    if (s.grid.y > 1 || s.grid.x > ea.capacity) return hipErrorNotSupported;
-    ea.blocks = s.grid.x;
-  }
-  size_t lds = s.lds;
-  if (EPI != EPI_STORE && lds < size_t(s.o.P) * g.nv * sizeof(double)) lds = size_t(s.o.P) * g.nv * sizeof(double);
-  hipLaunchKernelGGL((wilson_flat_kernel<EO, ADJ, CLOV, LW, EPI, S, T, VW, NVC>), s.grid, s.block, lds, st, g, s.o,
-                     knobs().xcd.get(1), a.parity, (const W*)a.Uf, (const W*)a.Ub, (const W*)a.in, (W*)a.out,
-                     (const W*)a.add, (const W*)a.clover, T(a.c_add), T(a.c_hop), ea);
+  hipLaunchKernelGGL((wilson_flat_kernel<ADJ, CLOV, LW, S, T, VW, NVC>), s.grid, s.block, s.lds, st, g, s.o,
+                     knobs().xcd.get(1), (const W*)a.U, (const W*)a.in, (W*)a.out, (const W*)a.clover, T(4.0 + a.mass));
   return hipGetLastError();
 }
 
-// The forms of one (storage, columns per lane): plain, with the clover term or
-// compressed links (full lattice), and the solver's fused epilogues (D or M
-// with EPI_NORM, their adjoints with EPI_AXPY; not FP64).
-template <bool EO, class S, class T, int VW, int NVC = 0>
-static hipError_t flat_forms(bool adj, const Geom& g, const FlatArgs& a, bool compressed, int epi, hipStream_t st,
-                             EpiArgs& ea) {
-  if (epi != EPI_STORE) {
-    if constexpr (sizeof(T) == 4) {
-      if (a.clover || compressed) return hipErrorNotSupported;
-      if (epi == EPI_NORM && !adj) return flat_launch<EO, false, false, 9, EPI_NORM, S, T, VW, NVC>(g, a, st, ea);
-      if (epi == EPI_AXPY && adj) return flat_launch<EO, true, false, 9, EPI_AXPY, S, T, VW, NVC>(g, a, st, ea);
-    }
-    return hipErrorNotSupported;
+// The forms of one (storage, columns per lane): plain, with the clover term and, but
+// for one FP32 column a lane (the direct kernel's), with compressed links.
+template <class S, class T, int VW, int NVC = 0>
+static hipError_t flat_forms(bool adj, const Geom& g, const FlatArgs& a, bool compressed, hipStream_t st) {
+  if (a.clover)
+    return adj ? flat_launch<true, true, 9, S, T, VW, NVC>(g, a, st) : flat_launch<false, true, 9, S, T, VW, NVC>(g, a, st);
+  if (compressed) {
+    if constexpr (VW > 1 || sizeof(T) == 8)
+      return adj ? flat_launch<true, false, 6, S, T, VW, NVC>(g, a, st)
+                 : flat_launch<false, false, 6, S, T, VW, NVC>(g, a, st);
+    else
+      return hipErrorNotSupported;
   }
-  if constexpr (!EO) {
-    if (a.clover)
-      return adj ? flat_launch<EO, true, true, 9, EPI_STORE, S, T, VW, NVC>(g, a, st, ea)
-                 : flat_launch<EO, false, true, 9, EPI_STORE, S, T, VW, NVC>(g, a, st, ea);
-    if (compressed)
-      return adj ? flat_launch<EO, true, false, 6, EPI_STORE, S, T, VW, NVC>(g, a, st, ea)
-                 : flat_launch<EO, false, false, 6, EPI_STORE, S, T, VW, NVC>(g, a, st, ea);
-  }
-  return adj ? flat_launch<EO, true, false, 9, EPI_STORE, S, T, VW, NVC>(g, a, st, ea)
-             : flat_launch<EO, false, false, 9, EPI_STORE, S, T, VW, NVC>(g, a, st, ea);
+  return adj ? flat_launch<true, false, 9, S, T, VW, NVC>(g, a, st) : flat_launch<false, false, 9, S, T, VW, NVC>(g, a, st);
 }
 
 // 16-bit storage.
-template <bool EO, class S>
-static hipError_t flat_forms16(int vw, bool adj, const Geom& g, const FlatArgs& a, bool compressed, int epi,
-                               hipStream_t st, EpiArgs& ea) {
+template <class S>
+static hipError_t flat_forms16(int vw, bool adj, const Geom& g, const FlatArgs& a, bool compressed, hipStream_t st) {
   switch (vw) {
-    case 4: return flat_forms<EO, S, float, 4>(adj, g, a, compressed, epi, st, ea);
-    case 2: return flat_forms<EO, S, float, 2>(adj, g, a, compressed, epi, st, ea);
+    case 4: return flat_forms<S, float, 4>(adj, g, a, compressed, st);
+    case 2: return flat_forms<S, float, 2>(adj, g, a, compressed, st);
   }
-  return flat_forms<EO, S, float, 1>(adj, g, a, compressed, epi, st, ea);
+  return flat_forms<S, float, 1>(adj, g, a, compressed, st);
 }
 
-template <bool EO>
-static hipError_t flat_forms_wide(int dtype, int vw, bool adj, const Geom& g, const FlatArgs& a, bool compressed,
-                                  int epi, hipStream_t st, EpiArgs& ea) {
-  // NVC: N_v known at compile time, so that the offsets of a site's components
-  // are part of the load instructions.
-  if (dtype == DT_C128)
-    return g.nv == 12 ? flat_forms<EO, C128, double, 1, 12>(adj, g, a, compressed, epi, st, ea)
-                      : flat_forms<EO, C128, double, 1>(adj, g, a, compressed, epi, st, ea);
-  return vw == 2 ? flat_forms<EO, C64, float, 2>(adj, g, a, compressed, epi, st, ea)
-                 : flat_forms<EO, C64, float, 1>(adj, g, a, compressed, epi, st, ea);
-}
-
-// Full lattice, BF16 and F16 storage (wilson_flat16.hip).
-hipError_t launch_wilson_flat16(int dtype, int vw, bool adj, const Geom& g, const FlatArgs& a, bool compressed, int epi,
-                                hipStream_t st, EpiArgs& ea);
+// BF16 and F16 storage (wilson_flat16.hip).
+hipError_t launch_wilson_flat16(int dtype, int vw, bool adj, const Geom& g, const FlatArgs& a, bool compressed,
+                                hipStream_t st);
 
 }  // namespace dsl
