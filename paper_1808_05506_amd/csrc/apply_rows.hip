@@ -1,99 +1,8 @@
 // Row-staged D_W and even-odd hop: which launches take the kernels of
-// wilson_rows.hpp, and in which shape.
-#include "wilson_rows.hpp"
+// wilson_rows.hpp (rows_shape.hpp: in which shape).
+#include "rows_shape.hpp"
 
 namespace dsl {
-
-// Sites per chunk R and halo sites hn.  A chunk of one x-row (hn = 2) where the
-// fewest chunks of at most 16 sites (more where fewer than 128 lanes would
-// result) divide the row and leave at most a tenth of the lanes idle: it has the
-// fewest halo loads and registers (16^3 x 32, N_v = 12: 92.5 us against 107.6
-// with hn = 4; FP32 N_v = 24 alone is faster with hn = 4: 184 us against 192, 951
-// against 995 on 24^3 x 48).  Elsewhere chunks across row ends of at most 256 lanes (hn =
-// 4), and of those from the longest down to half of it the one that leaves
-// the fewest lanes idle in the last chunk of the plane and the last wave
-// (24^3 x 48: 499 us at R = 21 against 601 with rows of 12; 34^3 x 68: 2225
-// against 2813).  DSLASH_ROW_SITES overrides R (hn = 4); false: no such kernel
-// (fewer than 64 lanes, or a chunk too short for its halo).  DSLASH_ROWS=2 asks
-// for these kernels where a chunk of one x-row alone holds its halo.
-// late: no such whole chunks of a row (whatever hn the launch takes).
-// pp: the buffer scheme (the one-row kernels: 0); two workgroups a CU need 80 KB.
-static bool rows_shape(const Geom& g, int dtype, int pp, bool any_nv, bool knob_form, int& R, int& hn,
-                       bool& late) {
-  const int nv = g.nv, wb = int(dtype_bytes(dtype));
-  const uint32_t plane = uint32_t(g.n[0]) * uint32_t(g.n[1]);
-  if (knobs().rows.get(1) == 2) {
-    if (any_nv) return false;
-    int r = knobs().row_sites.get(row_sites_default(g.n[0], nv));
-    if (r > g.n[0]) r = g.n[0];
-    if (r < 1 || r * nv > 256 || r * nv < 64 || !halo_fits(r, nv, wb, 2)) return false;
-  }
-  const int whole = row_sites_default(g.n[0], nv);
-  late = any_nv || whole <= 0 || g.n[0] % whole != 0 || 10 * whole * nv < 9 * ((whole * nv + 63) / 64) * 64 ||
-         whole * nv > 256 || !halo_fits(whole, nv, wb, 2);
-  hn = 4;
-  if (knobs().row_sites.set) {
-    R = knobs().row_sites.value;
-    if (R > int(plane)) R = int(plane);
-  } else {
-    R = whole;
-    if (!late && !knob_form) {
-      hn = nv > 16 && dtype == DT_C64 && halo_fits(R, nv, wb, 4) ? 4 : 2;
-      return true;
-    }
-    int rmax = 256 / nv;
-    if (rmax < 1) return false;
-    while (rmax > 1 && march_lds(rmax, nv, wb, pp, 4) > 76 * 1024) --rmax;
-    if (uint32_t(rmax) > plane) rmax = int(plane);
-    R = rmax;
-    uint64_t cost = 0;
-    for (uint32_t k = (plane + uint32_t(rmax) - 1) / uint32_t(rmax);; ++k) {  // chunks per plane
-      const int r = int((plane + k - 1) / k);
-      if (2 * r < rmax || !halo_fits(r, nv, wb, 4)) break;
-      const uint64_t lanes = uint64_t(k) * uint32_t((r * nv + 63) / 64);
-      if (cost == 0 || 100 * lanes < 97 * cost) {
-        cost = lanes;
-        R = r;
-      }
-      if (r == 1) break;
-    }
-  }
-  return R >= 1 && R * nv <= 256 && R * nv >= 64 && halo_fits(R, nv, wb, 4);
-}
-
-// t steps per workgroup: 8, or of the segment counts between that and 16 (FP32
-// storage) steps the one whose rounds of resident workgroups (two waves per
-// SIMD with two or more row buffers, three with one, and the LDS) march the
-// fewest steps, where the grid is a few rounds (more than 8 steps for a single
-// round only); a segment costs 0.7 of a step more (its first one stages a row
-// more).  On 16^3 x 32: N_v = 12 and 16 take
-// 16 steps (512 workgroups at two a CU); N_v = 4 and 8 took 44.4 and 65.6 us at
-// 8 steps against 64.8 and 74.6 us at 16.  Small lattices take shorter
-// segments until every SIMD has a wave.
-static int march_tsteps(const Geom& g, int R, int hn, int pp, int dtype) {
-  const uint32_t nt = uint32_t(g.n[3]), cus = uint32_t(device_cus());
-  const uint32_t wg_waves = uint32_t((R * g.nv + 63) / 64);
-  const auto grid = [&](uint32_t nseg) { return make_flat_march(g, uint32_t(R), (nt + nseg - 1) / nseg).grid; };
-  uint32_t per_cu = (pp ? 8u : 12u) / wg_waves;
-  const uint32_t by_lds = uint32_t(160 * 1024 / march_lds(R, g.nv, int(dtype_bytes(dtype)), pp, hn));
-  if (per_cu > by_lds) per_cu = by_lds;
-  if (per_cu < 1) per_cu = 1;
-  uint32_t best = (nt + 7) / 8;
-  if (grid(best) <= 4 * per_cu * cus) {
-    double cost = -1;
-    for (uint32_t n = dtype == DT_C64 ? (nt + 15) / 16 : best; n <= 2 * best; ++n) {
-      const uint32_t T = (nt + n - 1) / n;
-      const double c = double((grid(n) + per_cu * cus - 1) / (per_cu * cus)) * (T + 0.7);
-      if ((T <= 8 || grid(n) <= per_cu * cus) && grid(n) * wg_waves >= 4u * cus && (cost < 0 || c < cost)) {
-        cost = c;
-        best = n;
-      }
-    }
-  }
-  uint32_t T = (nt + best - 1) / best;
-  while (T > 1 && make_flat_march(g, uint32_t(R), T).grid * wg_waves < 4u * cus) T = (T + 1) / 2;
-  return int(T);
-}
 
 // Small lattices of 16-bit storage are faster by the direct kernel, which has more
 // lanes in flight: below `lanes` (site, column) pairs, unless a tuning variable or

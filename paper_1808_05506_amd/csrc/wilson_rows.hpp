@@ -913,14 +913,15 @@ __device__ __forceinline__ void march_step_pp(const Geom& g, const FlatChunk<HN>
 // and receives the +t row at the end of the step, which is then the next
 // step's own row; ba and bb take the other rows in turn (one barrier per staged
 // row) and the output.  The own row is gone from bo when the output is formed:
-// lattices whose rows are made of whole chunks fold the diagonal term into acc as
-// -2 diag psi at the start (16^3 x 32, FP32: 91.8 us against 95.6), the others
-// (late) read the own row once more before the +t row takes its place and add
-// diag psi last, as the direct kernel does (error against FP64, relative: 4.8e-8 against 7.7e-8).
+// in BF16, and where N_x lets rows of every block size be made of whole chunks
+// (rows_fold), the diagonal term is folded into acc as -2 diag psi at the start (16^3 x
+// 32, FP32: 91.8 us against 95.6), elsewhere (late; LATE for chunks of one x-row) the own
+// row is read once more before the +t row takes its place and diag psi added last, as
+// the direct kernel does (error against FP64, relative: 4.8e-8 against 7.7e-8).
 // LDS: bo [(R + HN) SSW], ba, bb [R SSW], lown, lnba, lnbb [R LW].
 // HALF: the +-y, +-z and first -t rows go through ba and bb as half spinors
 // (ba, bb [R HSW], adjacent), and the output through ba and bb together.
-template <bool FIRST, int DEPTH, bool ADJ, int NV, class S, class T, int LW, bool HALF = false, int EPI = EPI_STORE, int HN, int RN>
+template <bool FIRST, int DEPTH, bool ADJ, int NV, class S, class T, int LW, bool HALF, int EPI, bool LATE, int HN, int RN>
 __device__ __forceinline__ void march_step_o(const Geom& g, const FlatChunk<HN>& c, const FlatChunk<HN>& cn,
                                              const typename S::word* __restrict__ U,
                                              const typename S::word* __restrict__ in,
@@ -934,7 +935,7 @@ __device__ __forceinline__ void march_step_o(const Geom& g, const FlatChunk<HN>&
                                              u32x4 (&lr)[LinkK<S, NV, LW>::value + 1], cpx<T> (&carry)[2][3], EpiLane<S>& ep) {
   using W = typename S::word;
   using Q = MarchSeqO<FIRST>;
-  late = HN == 4 && late;
+  if constexpr (HN == 2) late = LATE;
   constexpr int LK = LinkK<S, NV, LW>::value;
   constexpr int SW = 12 * NV, CH = RowPieces<S>::CH;
   constexpr int SSW = SiteStride<NV, S>::WORDS, SSP = SiteStride<NV, S>::PIECES;
@@ -1065,7 +1066,7 @@ __device__ __forceinline__ void march_step_o(const Geom& g, const FlatChunk<HN>&
 // same with half-spinor neighbour rows (FP32 storage).
 template <int PP, int DEPTH> struct MarchOcc { static constexpr int value = PP ? 2 : MarchWaves<DEPTH>::value; };
 
-template <int DEPTH, bool ADJ, int NV, class S, class T, int LW, int PP, int EPI, int HN>
+template <int DEPTH, bool ADJ, int NV, class S, class T, int LW, int PP, int EPI, int HN, bool LATE>
 __global__ void __launch_bounds__(256, (MarchOcc<PP, DEPTH>::value))
     wilson_march_kernel(Geom g, FlatMarch m, int xcd, const typename S::word* __restrict__ U,
                         const typename S::word* __restrict__ in, typename S::word* __restrict__ out, T diag,
@@ -1114,7 +1115,7 @@ __global__ void __launch_bounds__(256, (MarchOcc<PP, DEPTH>::value))
   if constexpr (DEPTH > 4) DSL_PISSUE(4);
 #undef DSL_PISSUE
   if constexpr (PP >= 2)
-    march_step_o<true, DEPTH, ADJ, NV, S, T, LW, PP == 3, EPI>(g, c, cn, U, in, out, buf, buf1, buf2, lown, lnb, lnb1, xs,
+    march_step_o<true, DEPTH, ADJ, NV, S, T, LW, PP == 3, EPI, LATE>(g, c, cn, U, in, out, buf, buf1, buf2, lown, lnb, lnb1, xs,
                                                                R, xl, v, tid, nth, diag, m.late, r0, r1, r2, r3, r4, r5,
                                                                r6, lr, carry, ep);
   else if constexpr (PP == 1)
@@ -1131,7 +1132,7 @@ __global__ void __launch_bounds__(256, (MarchOcc<PP, DEPTH>::value))
       cn.plane += uint32_t(g.stride[3]);
     }
     if constexpr (PP >= 2)
-      march_step_o<false, DEPTH, ADJ, NV, S, T, LW, PP == 3, EPI>(g, c, cn, U, in, out, buf, buf1, buf2, lown, lnb, lnb1,
+      march_step_o<false, DEPTH, ADJ, NV, S, T, LW, PP == 3, EPI, LATE>(g, c, cn, U, in, out, buf, buf1, buf2, lown, lnb, lnb1,
                                                                   xs, R, xl, v, tid, nth, diag, m.late, r0, r1, r2, r3, r4, r5,
                                                                   r6, lr, carry, ep);
     else if constexpr (PP == 1)
@@ -1167,9 +1168,18 @@ static hipError_t march_launch(bool adj, int epi, dim3 grid, dim3 block, size_t 
                                const FlatMarch& m, bool xcd, const void* U, const void* in,
                                void* out, T diag, const EpiArgs& ea) {
   using W = typename S::word;
-#define DSL_MK(A, E)                                                                                              \
-  hipLaunchKernelGGL((wilson_march_kernel<DEPTH, A, NV, S, T, LW, PP, E, HN>), grid, block, lds, st, g, m, int(xcd), \
-                     (const W*)U, (const W*)in, (W*)out, diag, ea)
+#define DSL_MKL(A, E, LATE)                                                                                   \
+  hipLaunchKernelGGL((wilson_march_kernel<DEPTH, A, NV, S, T, LW, PP, E, HN, LATE>), grid, block, lds, st, g, m, \
+                     int(xcd), (const W*)U, (const W*)in, (W*)out, diag, ea)
+// (BF16 in chunks of one x-row is never late, chunks across row ends read m.late)
+#define DSL_MK(A, E)                                    \
+  do {                                                  \
+    if constexpr (HN == 2 && PP == 3) {                 \
+      if (m.late) DSL_MKL(A, E, true); else DSL_MKL(A, E, false); \
+    } else {                                            \
+      DSL_MKL(A, E, false);                             \
+    }                                                   \
+  } while (0)
   if (epi == EPI_STORE) {
     if (adj) DSL_MK(true, EPI_STORE); else DSL_MK(false, EPI_STORE);
   } else if constexpr (MarchEpiBuilt<PP, DEPTH, LW, NV, HN>::value) {
@@ -1180,6 +1190,7 @@ static hipError_t march_launch(bool adj, int epi, dim3 grid, dim3 block, size_t 
     return hipErrorNotSupported;
   }
 #undef DSL_MK
+#undef DSL_MKL
   return hipGetLastError();
 }
 

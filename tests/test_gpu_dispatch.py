@@ -63,3 +63,30 @@ def test_staggered_flat(dims, dt, nvs, monkeypatch):
         assert differ or dt in ("bf16", "f16")  # (16-bit stores round the difference away)
         compare(down(D.apply_compressed("staggered", VC, P, 0.1)), compress.apply("staggered", vc, p, 0.1, False), dt,
                 f"D_S compressed nv={nv}")
+
+
+# Rows of 16 sites add the diagonal term first, rows of 20, 24 and 28 last (C64); the
+# blocks of one row take chunks of one x-row or across row ends as their lanes allow
+@pytest.mark.parametrize("dt", ["c64", "bf16"])
+@pytest.mark.parametrize("nx", [20, 24, 28])
+def test_columns_do_not_depend_on_the_block_size(dt, nx, monkeypatch):
+    # at a fixed t-segment length and in one buffer scheme, a block of 24 columns equals
+    # its blocks of 4, 8, 12 and (the first) 16 columns bit for bit
+    dims = (nx, 4, 4, 16)
+    say(f"case block-size invariance {dims} {dt}")
+    u = rounded(synthetic.gauge_links(dims, "haar", 920), dt)
+    p = rounded(synthetic.wilson_spinor(dims, 24, 921), dt)
+    U, P = up(u, dt), up(p, dt)
+    set_knob(monkeypatch, "DSLASH_ROWS", "1")
+    set_knob(monkeypatch, "DSLASH_TSTEPS", "8")
+    set_knob(monkeypatch, "DSLASH_MARCH_PP", "3" if dt == "c64" else "2")
+    axis = -1 if dt == "c64" else -2
+    for adj in (False, True):
+        full = D.apply("wilson", U, P, 0.1, adjoint=adj)
+        compare(down(full), wilson.apply(u, p, 0.1, adj), dt, f"D_W {dims} adj={adj}")
+        for k in (4, 8, 12, 16):
+            for c0 in range(0, 24 - k + 1, k):
+                sl = [slice(None)] * full.dim()
+                sl[axis] = slice(c0, c0 + k)
+                part = D.apply("wilson", U, P[tuple(sl)].contiguous(), 0.1, adjoint=adj)
+                assert torch.equal(part, full[tuple(sl)]), (k, c0)

@@ -20,6 +20,7 @@ NOT_SUPPORTED = 801  # hipErrorNotSupported: left to the direct kernel
 
 SOURCE = r"""
 #include "flat_order.hpp"
+#include "rows_shape.hpp"
 #include <vector>
 using namespace dsl;
 
@@ -64,6 +65,23 @@ int flat_missed(const int* d, int nv, int comps, int wb, int vw) {
   }
   for (int n : seen) bad += n != 1;
   return bad;
+}
+
+// out: R, halo sites, diagonal term last; 0 where the row-staged D_W march does not apply
+int rows(int dtype, const int* d, int nv, int pp, int* out) {
+  const bool any = nv != 4 && nv != 8 && nv != 12 && nv != 16 && nv != 24;
+  bool late = false;
+  const bool ok = rows_shape(geom(d, nv), dtype, pp, any, false, out[0], out[1], late);
+  out[2] = late;
+  return ok;
+}
+
+// out: chunks, planes of a tile of the one-row order; returns the chunks per plane
+int one_row(const int* d, int R, int site_bytes, int* out) {
+  const FlatMarch m = one_row_order(geom(d, 1), R, site_bytes);
+  out[0] = int(m.kb);
+  out[1] = int(m.zb);
+  return int(m.chunks);
 }
 
 // The launchers on null fields, for calls that they refuse before they launch.
@@ -148,3 +166,21 @@ def test_rows_0_leaves_every_call_to_the_direct_kernels(shapes, dtype, nv, monke
     finally:
         monkeypatch.undo()
         shapes.dslash_reload_tuning()
+
+
+PP = {C64: 3, BF16: 2, F16: 0}
+
+
+def _rows(lib, dtype, dims, nv):
+    out = (ctypes.c_int * 3)()
+    return tuple(out) if lib.rows(dtype, _dims(dims), nv, PP[dtype], out) else None
+
+
+@pytest.mark.parametrize("dtype", [C64, BF16, F16])
+@pytest.mark.parametrize("nx", list(range(2, 66)))
+def test_the_diagonal_term_does_not_depend_on_the_block_size(shapes, dtype, nx):
+    # whether it is added first or last: the same for each block size that has rows at all
+    late = {s[2] for s in (_rows(shapes, dtype, (nx, 12, 12, 12), nv) for nv in (4, 8, 12, 16, 24)) if s}
+    assert len(late) <= 1
+    # (a chunk of one x-row adds it last in C64 only)
+    assert late <= ({0, 1} if dtype == C64 else {0})
