@@ -26,11 +26,17 @@ inline bool rows_fold(int nx) {
 // Sites per chunk R and halo sites hn.  A chunk of one x-row (hn = 2) where the row is
 // made of whole ones: it has the fewest halo loads and registers (16^3 x 32, N_v = 12:
 // 92.5 us against 107.6 with hn = 4; BF16, N_v = 24: 129 against 164; FP32 N_v = 24 alone is
-// faster with hn = 4: 187 us against 193, 1570 against 1650 on 32^4).  Elsewhere chunks
-// across row ends of at most 256 lanes (hn = 4), and of those from the longest down to half
-// of it the one that leaves the fewest lanes idle in the last chunk of the plane and the
-// last wave (24^3 x 48: 499 us at R = 21 against 601 with rows of 12; 34^3 x 68: 2225 against
-// 2813).
+// faster with hn = 4, in the march only: 187 us against 193, 1570 against 1650 on 32^4),
+// and in C64 at N_v = 4
+// where a whole row leaves at most a quarter idle (28^4: 195 us against 244, 24^3 x 48 218
+// against 242; 62 %, 20^4, 73.0 against 69.4).
+// Elsewhere chunks across row ends (hn = 4).  N_v = 4: one wave (24^3 x 48: 242 us, 296 with
+// four; BF16 126 and 154).  Other N_v: at most 256 lanes, and of those from the longest
+// down to half of it the one that leaves the fewest lanes idle in the last chunk of the
+// plane and the last wave (24^3 x 48: 499 us at R = 21 against 601 with rows of 12; 34^3 x
+// 68: 2225 against 2813).  In the BF16 march three waves count as four: a CU holds eight, two
+// workgroups of either (N_v = 24, 14x13x12x16: 47 us at R = 10 against 62 at 8, 34x18x18x24 304
+// against 346; in C64 neither is always the faster).
 // DSLASH_ROW_SITES overrides R (hn = 4); false: no such kernel
 // (fewer than 64 lanes, or a chunk too short for its halo).  DSLASH_ROWS=2 asks
 // for these kernels where a chunk of one x-row alone holds its halo.
@@ -53,21 +59,23 @@ inline bool rows_shape(const Geom& g, int dtype, int pp, bool any_nv, bool knob_
     if (R > int(plane)) R = int(plane);
   } else {
     const int whole = row_sites_default(g.n[0], nv);
-    if (!any_nv && !knob_form && whole_chunks(g.n[0], nv, wb)) {
+    const bool row4 = nv == 4 && dtype == DT_C64 && g.n[0] == whole && g.n[0] >= 24 && g.n[0] <= 32;
+    if (!any_nv && !knob_form && (row4 || whole_chunks(g.n[0], nv, wb))) {
       R = whole;
-      hn = nv > 16 && dtype == DT_C64 && halo_fits(R, nv, wb, 4) ? 4 : 2;
+      hn = nv > 16 && dtype == DT_C64 && pp && halo_fits(R, nv, wb, 4) ? 4 : 2;
       return true;
     }
-    int rmax = 256 / nv;
+    int rmax = nv == 4 ? 16 : 256 / nv;
     if (rmax < 1) return false;
     while (rmax > 1 && march_lds(rmax, nv, wb, pp, 4) > 76 * 1024) --rmax;
     if (uint32_t(rmax) > plane) rmax = int(plane);
     R = rmax;
     uint64_t cost = 0;
-    for (uint32_t k = (plane + uint32_t(rmax) - 1) / uint32_t(rmax); ; ++k) {  // chunks per plane
+    for (uint32_t k = (plane + uint32_t(rmax) - 1) / uint32_t(rmax); nv != 4; ++k) {  // chunks per plane
       const int r = int((plane + k - 1) / k);
       if (2 * r < rmax || !halo_fits(r, nv, wb, 4)) break;
-      const uint64_t lanes = uint64_t(k) * uint32_t((r * nv + 63) / 64);
+      const uint32_t waves = uint32_t((r * nv + 63) / 64);
+      const uint64_t lanes = uint64_t(k) * (dtype == DT_BF16 && pp == 2 && waves == 3 ? 4 : waves);
       if (cost == 0 || 100 * lanes < 97 * cost) {
         cost = lanes;
         R = r;

@@ -184,3 +184,21 @@ def test_the_diagonal_term_does_not_depend_on_the_block_size(shapes, dtype, nx):
     assert len(late) <= 1
     # (a chunk of one x-row adds it last in C64 only)
     assert late <= ({0, 1} if dtype == C64 else {0})
+
+
+# Chunk and halo sites, us so and with the shape in brackets (one MI355X)
+@pytest.mark.parametrize("dtype,dims,nv,want", [
+    (C64, (24, 24, 24, 48), 4, (24, 2)),   # 218 (61, 4: 296; 16, 4: 242)
+    (C64, (28, 28, 28, 28), 4, (28, 2)),   # 195 (61, 4: 286; 16, 4: 244)
+    (C64, (20, 20, 20, 20), 4, (16, 4)),   # 69 (58, 4: 80; 20, 2: 73)
+    (C64, (34, 18, 18, 24), 4, (16, 4)),   # 110 (61, 4: 143)
+    (BF16, (24, 24, 24, 48), 4, (16, 4)),  # 126 (64, 4: 154; 24, 2: 162)
+    (F16, (14, 13, 12, 16), 4, (16, 4)),   # 15.9 (61, 4: 19.1)
+    (BF16, (14, 13, 12, 16), 24, (10, 4)),  # 47 (8, 4: 62)
+    (BF16, (34, 18, 18, 24), 24, (10, 4)),  # 304 (8, 4: 346)
+    (C64, (16, 16, 16, 32), 12, (16, 2)),
+    (C64, (16, 16, 16, 32), 24, (8, 4)),   # 187 (8, 2: 193)
+    (BF16, (16, 16, 16, 32), 24, (8, 2)),  # 129 (8, 4: 164)
+])
+def test_rows_take_the_faster_chunk(shapes, dtype, dims, nv, want):
+    assert _rows(shapes, dtype, dims, nv)[:2] == want
