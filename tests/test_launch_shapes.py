@@ -202,3 +202,13 @@ def test_the_diagonal_term_does_not_depend_on_the_block_size(shapes, dtype, nx):
 ])
 def test_rows_take_the_faster_chunk(shapes, dtype, dims, nv, want):
     assert _rows(shapes, dtype, dims, nv)[:2] == want
+
+
+# The even-odd hop in C64, us with tiles that divide the lattice and with larger ones:
+# 32^4, N_v = 4 193 and 204; 24^3 x 48, N_v = 12 272 and 294
+@pytest.mark.parametrize("packed,R,nv", [((16, 32, 32, 32), 16, 4), ((16, 32, 32, 32), 16, 8), ((12, 24, 24, 48), 12, 12)])
+def test_one_row_tiles_divide_the_lattice(shapes, packed, R, nv):
+    out = (ctypes.c_int * 2)()
+    chunks = shapes.one_row(_dims(packed), R, 12 * nv * 8, out)
+    assert chunks % out[0] == 0 and packed[2] % out[1] == 0, list(out)
+    assert out[0] * out[1] * R * 12 * nv * 8 <= 1280 * 1024
