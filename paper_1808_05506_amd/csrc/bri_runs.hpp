@@ -2,6 +2,7 @@
 // the spins of a run at a time: for D_B and its gradient with respect to W.
 #pragma once
 
+#include "bri_shape.hpp"
 #include "chunks.hpp"
 #include "launch.hpp"
 #include "rows.hpp"
@@ -147,21 +148,5 @@ struct RunStage {
     }
   }
 };
-
-// The widest block of the fewest idle columns.
-inline int bri_block(int dtype, int nv) {
-  static const int widths64[] = {24, 16, 12, 10, 8, 6, 4}, widths128[] = {12, 8, 6, 4};
-  const int* w = dtype == DT_C64 ? widths64 : widths128;
-  const int nw = dtype == DT_C64 ? 7 : 4;
-  int nb = w[0], cols = 0;
-  for (int k = 0; k < nw; ++k) {
-    const int n = (nv + w[k] - 1) / w[k] * w[k];
-    if (cols == 0 || n < cols) {
-      cols = n;
-      nb = w[k];
-    }
-  }
-  return nb;
-}
 
 }  // namespace dsl

@@ -341,35 +341,29 @@ hipError_t bri_flat_t(const BriCall& a) {
   return hipGetLastError();
 }
 
-template <int NB, int P>
+template <int NB>
 hipError_t bri_flat_c64(const BriCall& a, bool pairs) {
+  constexpr int P = bri_sites(DT_C64, NB);
   return pairs ? bri_flat_t<BriBlock<C64, NB, P, BRI_PAIRS>, C64, float>(a)
                : bri_flat_t<BriBlock<C64, NB, P, BRI_WORDS>, C64, float>(a);
 }
 
-template <int NB, int P>
+template <int NB>
 hipError_t bri_flat_c128(const BriCall& a) {
-  return bri_flat_t<BriBlock<C128, NB, P, BRI_WIDE>, C128, double>(a);
+  return bri_flat_t<BriBlock<C128, NB, bri_sites(DT_C128, NB), BRI_WIDE>, C128, double>(a);
 }
 
 }  // namespace
 
-// D_B for C64 and C128; hipErrorNotSupported where the direct kernel is taken:
-// other storages, misaligned pointers, planes of 4 GB, DSLASH_ROWS=0, and C64
-// with less than a wave per SIMD (one right-hand side in a lane either way, and
-// the 27 runs one after the other: 8^4, N_v = 12 71 us against 68, N_v = 4 76
-// against 62; 12 x 8^3, N_v = 12 81 against 82) or N_v = 1 and 3 (a quarter and
-// more of the lanes idle, 16^3 x 32: 765 us against 398, 805 against 675; N_v = 5:
-// 761 against 778).  DSLASH_BRI_LANES: fewest (site, column) pairs in C64 (set, also
-// N_v = 1 and 3).  DSLASH_ROWS=2: this kernel where brillouin_rows_cover says so.
+// D_B for C64 and C128; hipErrorNotSupported where the direct kernel is taken: other
+// storages, misaligned FP64, planes of 4 GB, DSLASH_ROWS=0, and where this one does not
+// pay (brillouin_flat_pays).  DSLASH_ROWS=2: this kernel where brillouin_rows_cover says so.
 hipError_t launch_brillouin_flat(bool adj, int dtype, const Geom& g, const void* Wl, const void* in, void* out,
                                  double mass, hipStream_t st, const void* clover) {
   const int rows = knobs().rows.get(1);
   if (rows == 0 || (dtype != DT_C64 && dtype != DT_C128)) return hipErrorNotSupported;
   if (rows == 2 && !brillouin_rows_cover(dtype, g, clover != nullptr)) return hipErrorNotSupported;
-  if (rows != 2 && dtype == DT_C64 && !knobs().bri_lanes.set && (g.nv == 1 || g.nv == 3)) return hipErrorNotSupported;
-  if (rows != 2 && dtype == DT_C64 && size_t(g.vol) * size_t(g.nv) < size_t(knobs().bri_lanes.get(256 * device_cus())))
-    return hipErrorNotSupported;
+  if (rows != 2 && !brillouin_flat_pays(dtype, g)) return hipErrorNotSupported;
   const size_t wb = dtype_bytes(dtype), plane = size_t(g.n[0]) * size_t(g.n[1]) * wb;
   if (plane * 360 >= (size_t(1) << 32) || plane * 12 * size_t(g.nv) >= (size_t(1) << 32)) return hipErrorNotSupported;
   if (dtype == DT_C128 && !(aligned16(Wl) && aligned16(in) && aligned16(out) && aligned16(clover)))
@@ -379,21 +373,21 @@ hipError_t launch_brillouin_flat(bool adj, int dtype, const Geom& g, const void*
   if (dtype == DT_C64) {
     const bool pairs = g.nv % 2 == 0 && aligned16(in);
     switch (nb) {
-      case 24: return bri_flat_c64<24, 8>(a, pairs);
-      case 16: return bri_flat_c64<16, 16>(a, pairs);
-      case 12: return bri_flat_c64<12, 21>(a, pairs);
-      case 10: return bri_flat_c64<10, 25>(a, pairs);
-      case 8: return bri_flat_c64<8, 32>(a, pairs);
-      case 6: return bri_flat_c64<6, 42>(a, pairs);
+      case 24: return bri_flat_c64<24>(a, pairs);
+      case 16: return bri_flat_c64<16>(a, pairs);
+      case 12: return bri_flat_c64<12>(a, pairs);
+      case 10: return bri_flat_c64<10>(a, pairs);
+      case 8: return bri_flat_c64<8>(a, pairs);
+      case 6: return bri_flat_c64<6>(a, pairs);
     }
-    return bri_flat_c64<4, 64>(a, pairs);
+    return bri_flat_c64<4>(a, pairs);
   }
   switch (nb) {
-    case 12: return bri_flat_c128<12, 20>(a);
-    case 8: return bri_flat_c128<8, 32>(a);
-    case 6: return bri_flat_c128<6, 42>(a);
+    case 12: return bri_flat_c128<12>(a);
+    case 8: return bri_flat_c128<8>(a);
+    case 6: return bri_flat_c128<6>(a);
   }
-  return bri_flat_c128<4, 64>(a);
+  return bri_flat_c128<4>(a);
 }
 
 }  // namespace dsl

@@ -249,19 +249,15 @@ hipError_t bri_wgrad_c128(const GradCall& a) {
 
 }  // namespace
 
-// hipErrorNotSupported where the direct kernel is taken: misaligned FP64, planes of
-// 4 GB, DSLASH_ROWS=0, C64 with less than a wave per SIMD (8^4, N_v = 12: 84 us here,
-// 63 there; 12 x 8^3: 97 and 125) and FP64 below N_v = 4 (12^3 x 16, N_v = 2: 438 us
-// and 283; N_v = 4: 460 and 522).  DSLASH_BRI_LANES, DSLASH_ROWS=2: as in D_B (the
-// latter in C64 only).
+// hipErrorNotSupported where the direct kernel is taken: misaligned FP64, planes of 4 GB,
+// DSLASH_ROWS=0, and where this one does not pay (brillouin_wgrad_pays).
+// DSLASH_ROWS=2: as in D_B, in C64 only.
 hipError_t launch_brillouin_wgrad_flat(int dtype, const Geom& g, const void* chi, const void* psi, void* GW,
                                        hipStream_t st) {
   const int rows = knobs().rows.get(1);
   if (rows == 0 || (dtype != DT_C64 && dtype != DT_C128)) return hipErrorNotSupported;
   if (rows == 2 && (dtype != DT_C64 || !brillouin_rows_cover(dtype, g, false))) return hipErrorNotSupported;
-  const bool any = rows == 2 || knobs().bri_lanes.set;
-  if (!any && dtype == DT_C64 && size_t(g.vol) * size_t(g.nv) < size_t(256 * device_cus())) return hipErrorNotSupported;
-  if (!any && dtype == DT_C128 && g.nv < 4) return hipErrorNotSupported;
+  if (rows != 2 && !brillouin_wgrad_pays(dtype, g)) return hipErrorNotSupported;
   const size_t plane = size_t(g.n[0]) * size_t(g.n[1]) * dtype_bytes(dtype);
   if (plane * 12 * size_t(g.nv) >= (size_t(1) << 32)) return hipErrorNotSupported;
   if (dtype == DT_C128 && !(aligned16(chi) && aligned16(psi) && aligned16(GW))) return hipErrorNotSupported;

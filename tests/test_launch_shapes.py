@@ -19,6 +19,7 @@ C64, C128, BF16, F16 = 0, 1, 2, 3
 NOT_SUPPORTED = 801  # hipErrorNotSupported: left to the direct kernel
 
 SOURCE = r"""
+#include "bri_shape.hpp"
 #include "flat_order.hpp"
 #include "rows_shape.hpp"
 #include <vector>
@@ -83,6 +84,10 @@ int one_row(const int* d, int R, int site_bytes, int* out) {
   out[1] = int(m.zb);
   return int(m.chunks);
 }
+
+int brillouin_pays(int dtype, const int* d, int nv) { return brillouin_flat_pays(dtype, geom(d, nv)); }
+int wgrad_pays(int dtype, const int* d, int nv) { return brillouin_wgrad_pays(dtype, geom(d, nv)); }
+int brillouin_block(int dtype, int nv) { return bri_block(dtype, nv); }
 
 // The launchers on null fields, for calls that they refuse before they launch.
 int launch_wilson(int dtype, const int* d, int nv, int clover, int compressed) {
@@ -212,3 +217,38 @@ def test_one_row_tiles_divide_the_lattice(shapes, packed, R, nv):
     chunks = shapes.one_row(_dims(packed), R, 12 * nv * 8, out)
     assert chunks % out[0] == 0 and packed[2] % out[1] == 0, list(out)
     assert out[0] * out[1] * R * 12 * nv * 8 <= 1280 * 1024
+
+
+# D_B by the kernel that stages the runs, and by the direct one (us, one MI355X)
+@pytest.mark.parametrize("dtype,dims,nv,us,direct", [
+    (C128, (4, 4, 4, 4), 12, 73, 59), (C128, (4, 4, 4, 4), 24, 72, 59), (C128, (8, 8, 8, 8), 3, 117, 97),
+    (C128, (16, 8, 8, 16), 4, 128, 106), (C128, (12, 12, 12, 12), 4, 166, 195), (C128, (12, 12, 12, 16), 2, 259, 168),
+    (C128, (12, 12, 12, 16), 4, 273, 211), (C128, (14, 13, 12, 16), 4, 286, 336), (C128, (16, 16, 16, 16), 2, 362, 494),
+    (C128, (18, 14, 20, 26), 2, 780, 1039), (C128, (16, 16, 16, 32), 12, 1317, 2183), (C128, (8, 8, 8, 8), 5, 86, 106),
+    (C64, (8, 8, 8, 8), 12, 73, 69), (C64, (12, 12, 12, 16), 4, 155, 101), (C64, (12, 12, 12, 12), 5, 151, 106),
+    (C64, (12, 12, 12, 16), 5, 152, 167), (C64, (16, 16, 16, 32), 3, 355, 670), (C64, (12, 12, 12, 24), 1, 250, 172),
+    (C64, (32, 32, 32, 32), 12, 6200, 10000),
+])
+def test_brillouin_takes_the_faster_kernel(shapes, dtype, dims, nv, us, direct):
+    assert bool(shapes.brillouin_pays(dtype, _dims(dims), nv)) == (us < direct)
+
+
+# the gradient with respect to W
+@pytest.mark.parametrize("dtype,dims,nv,us,direct", [
+    (C128, (4, 4, 4, 4), 4, 147, 6.5), (C128, (4, 4, 4, 4), 20, 746, 25), (C128, (6, 6, 6, 8), 12, 153, 83),
+    (C128, (6, 6, 6, 8), 24, 332, 184), (C128, (8, 8, 8, 8), 12, 175, 213), (C128, (8, 8, 8, 8), 24, 372, 461),
+    (C128, (8, 8, 8, 8), 8, 163, 115), (C128, (12, 8, 8, 8), 5, 176, 136), (C128, (12, 8, 8, 8), 8, 181, 206),
+    (C128, (16, 16, 16, 32), 3, 1955, 2032), (C128, (16, 16, 16, 32), 12, 4092, 7810),
+    (C64, (6, 6, 6, 8), 48, 175, 121), (C64, (3, 9, 9, 9), 32, 162, 106), (C64, (8, 8, 8, 8), 20, 165, 131),
+    (C64, (8, 8, 8, 8), 24, 105, 150), (C64, (12, 8, 8, 8), 12, 97, 125), (C64, (16, 16, 16, 32), 12, 970, 3100),
+])
+def test_wgrad_takes_the_faster_kernel(shapes, dtype, dims, nv, us, direct):
+    want = us < direct and not (dtype == C128 and nv < 4)  # (below four columns it is the slower one elsewhere)
+    assert bool(shapes.wgrad_pays(dtype, _dims(dims), nv)) == want
+
+
+@pytest.mark.parametrize("dtype,nv,width", [(C128, 4, 4), (C128, 5, 6), (C128, 8, 8), (C128, 12, 12), (C128, 14, 8), (C128, 18, 12),
+                                            (C128, 20, 12), (C128, 28, 8), (C64, 4, 4), (C64, 5, 6), (C64, 12, 12), (C64, 24, 24),
+                                            (C64, 28, 16), (C64, 40, 8), (C64, 48, 24)])
+def test_brillouin_blocks_cost_least(shapes, dtype, nv, width):
+    assert shapes.brillouin_block(dtype, nv) == width
