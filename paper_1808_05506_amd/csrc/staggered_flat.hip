@@ -9,6 +9,7 @@
 // 18x14x20x26 C64 42 us (69 before), 34^4 428 (488); 22x18x20x16 FP64 71 (80);
 // 32^4 BF16 206 (269), FP16 200 (275); N_v = 7, 32^4 C64 269 (434), 22x18x20x16
 // FP64 54 (107).  Where they do, 32^4 C64 takes 284 us by rows, 300 here.
+#include "flat_rule.hpp"
 #include "wilson_flat.hpp"
 
 namespace dsl {
@@ -226,13 +227,7 @@ hipError_t launch_staggered_flat(bool adj, int dtype, const Geom& g, const void*
                                  double mass, hipStream_t st, bool compressed) {
   if (knobs().rows.get(1) == 0 || !flat_covers(g, dtype)) return hipErrorNotSupported;
   const int vw = flat_vw(dtype, g.nv, aligned16(in) && aligned16(out));
-  // Small lattices go to the direct kernel, which has a lane for every column.
-  // Fewest lanes for this one, us here and there: FP64 any from N_v = 4 on (8^4, N_v =
-  // 4 5.8 and 6.2), 256k below (N_v = 1, 65k 26.3 and 18.9); else 80k (C64 N_v = 4, 55k
-  // 7.4 and 6.2, N_v = 1, 65k 9.9 and 9.4; BF16 N_v = 4, 65k 10.3 and 6.4, N_v = 6, 83k 7.0
-  // and 7.6; four columns 128k: F16 N_v = 12, 83k 9.9 and 8.7, 196k 14.9 and 15.3).
-  const uint32_t fewest = dtype == DT_C128 ? (g.nv < 4 ? 256 : 0) : vw == 4 ? 128 : 80;
-  if (size_t(g.vol) * size_t(g.nv / vw) < size_t(knobs().flat_lanes.get(int(fewest * 1024)))) return hipErrorNotSupported;
+  if (!staggered_flat_pays(dtype, g, vw, compressed)) return hipErrorNotSupported;
   const StagCall a{adj, compressed, &g, U, in, out, mass, st};
   // NVC: as in the flat D_W kernels (N_v = 12: C64 24^3 x 48 196 us, 207 without; FP64
   // 22x18x20x16 69 and 71.5)

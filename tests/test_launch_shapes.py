@@ -21,6 +21,7 @@ NOT_SUPPORTED = 801  # hipErrorNotSupported: left to the direct kernel
 SOURCE = r"""
 #include "bri_shape.hpp"
 #include "flat_order.hpp"
+#include "flat_rule.hpp"
 #include "rows_shape.hpp"
 #include <vector>
 using namespace dsl;
@@ -85,6 +86,12 @@ int one_row(const int* d, int R, int site_bytes, int* out) {
   return int(m.chunks);
 }
 
+int wilson_pays(int dtype, const int* d, int nv, int clover, int compressed) {
+  return wilson_flat_pays(dtype, geom(d, nv), flat_vw(dtype, nv, true), clover, compressed);
+}
+int staggered_pays(int dtype, const int* d, int nv, int compressed) {
+  return staggered_flat_pays(dtype, geom(d, nv), flat_vw(dtype, nv, true), compressed);
+}
 int brillouin_pays(int dtype, const int* d, int nv) { return brillouin_flat_pays(dtype, geom(d, nv)); }
 int wgrad_pays(int dtype, const int* d, int nv) { return brillouin_wgrad_pays(dtype, geom(d, nv)); }
 int brillouin_block(int dtype, int nv) { return bri_block(dtype, nv); }
@@ -252,3 +259,32 @@ def test_wgrad_takes_the_faster_kernel(shapes, dtype, dims, nv, us, direct):
                                             (C64, 28, 16), (C64, 40, 8), (C64, 48, 24)])
 def test_brillouin_blocks_cost_least(shapes, dtype, nv, width):
     assert shapes.brillouin_block(dtype, nv) == width
+
+
+# The flat kernels and the direct one (us on inputs that change, one MI355X)
+@pytest.mark.parametrize("dtype,dims,nv,compressed,us,direct", [
+    (BF16, (20, 20, 20, 20), 4, 0, 28.3, 18.9), (F16, (24, 24, 24, 48), 4, 0, 93.4, 87.2),
+    (BF16, (18, 14, 20, 26), 2, 0, 17.4, 13.0), (BF16, (32, 32, 32, 32), 2, 0, 91.6, 104.1),
+    (BF16, (20, 20, 20, 20), 1, 0, 17.7, 16.4), (BF16, (24, 24, 24, 24), 12, 0, 55.0, 87.0),
+    (C64, (20, 20, 20, 40), 2, 0, 91.8, 74.8), (C64, (24, 24, 24, 24), 2, 0, 71.9, 79.9),
+    (C64, (12, 12, 12, 24), 4, 0, 11.4, 14.1), (BF16, (18, 14, 20, 26), 1, 1, 12.5, 8.7),
+    (BF16, (24, 24, 24, 48), 3, 1, 62.4, 60.6), (C64, (16, 16, 16, 32), 1, 1, 18.1, 15.1),
+    (C64, (20, 20, 20, 40), 2, 1, 43.3, 41.2), (C64, (16, 16, 16, 16), 4, 1, 11.1, 12.8),
+    (C128, (8, 8, 8, 8), 4, 0, 5.8, 6.2), (C128, (16, 16, 16, 16), 1, 0, 26.3, 18.9),
+])
+def test_staggered_flat_takes_what_it_is_faster_at(shapes, dtype, dims, nv, compressed, us, direct):
+    assert bool(shapes.staggered_pays(dtype, _dims(dims), nv, compressed)) == (us < direct)
+
+
+@pytest.mark.parametrize("dtype,dims,nv,clover,compressed,us,direct", [
+    (BF16, (16, 8, 8, 16), 32, 0, 0, 29.4, 24.7), (BF16, (8, 8, 8, 8), 7, 0, 0, 9.1, 8.4),
+    (F16, (8, 8, 8, 8), 7, 0, 0, 9.0, 10.7), (BF16, (17, 13, 11, 19), 7, 0, 0, 35.7, 39.5),
+    (BF16, (16, 8, 8, 16), 9, 0, 0, 18.1, 17.1), (BF16, (21, 15, 13, 27), 2, 0, 0, 29.7, 39.1),
+    (BF16, (12, 12, 12, 16), 6, 0, 0, 18.2, 22.1), (BF16, (12, 12, 12, 12), 3, 1, 0, 21.7, 16.2),
+    (BF16, (17, 13, 11, 19), 24, 1, 0, 76.9, 65.1), (BF16, (16, 16, 16, 16), 24, 1, 0, 103.8, 86.6),
+    (C128, (18, 14, 20, 26), 4, 1, 0, 164.7, 148.1), (C128, (24, 24, 24, 48), 12, 0, 0, 1050, 1906),
+    (F16, (17, 13, 11, 19), 28, 0, 1, 73.1, 66.9), (BF16, (20, 20, 20, 20), 20, 0, 1, 173.2, 199.4),
+    (C64, (21, 16, 17, 33), 4, 0, 1, 106, 85), (C64, (16, 16, 16, 32), 1, 0, 0, 66.4, 26.6),
+])
+def test_wilson_flat_takes_what_it_is_faster_at(shapes, dtype, dims, nv, clover, compressed, us, direct):
+    assert bool(shapes.wilson_pays(dtype, _dims(dims), nv, clover, compressed)) == (us < direct)
