@@ -65,7 +65,9 @@ inline bool flat_covers(const Geom& g, int dtype) {
 // the one that wastes the fewest lanes on the chunk count and the last wave.
 // zb x kb: whole planes whose spinors at one t take at most 1.2 MB where two fit,
 // else three planes of about a third of 1.05 MB each (FP64, N_v = 12, 16^3 x 32: 220 us
-// with 2 whole planes, 230 with 4 planes x 7 of 13 chunks).  D_W in pieces of 16 bytes
+// with 2 whole planes, 230 with 4 planes x 7 of 13 chunks); two planes where N_z is 4 or 5,
+// with chunks that divide the plane, as three leave a tile of one or two (64 x 4 x 4 x 16,
+// FP64, N_v = 24 84 us, 61 in two).  D_W in pieces of 16 bytes
 // takes two workgroups a CU (79 KB of LDS asked for): more of them in flight than that
 // push each other's neighbour rows out of the L2.  24^3 x 48, two, three and four a CU:
 // FP64, N_v = 12, 1141, 1167 and 1368 us; C64, N_v = 26, 1287, 1445 and 1590.  With the clover
@@ -98,10 +100,17 @@ inline FlatShape flat_shape(const Geom& g, int comps, int word_bytes, int vw, in
     s.o.zb = uint32_t(1.2 * 1024 * 1024 / full);
     if (s.o.zb > uint32_t(g.n[2])) s.o.zb = uint32_t(g.n[2]);
   } else {
-    s.o.zb = g.n[2] < 3 ? uint32_t(g.n[2]) : 3u;
+    const bool two_planes = g.n[2] == 4 || g.n[2] == 5;
+    s.o.zb = g.n[2] < 3 ? uint32_t(g.n[2]) : two_planes ? 2u : 3u;
     s.o.kb = uint32_t(1.05 * 1024 * 1024 / (s.o.zb * row));
     if (s.o.kb < 1) s.o.kb = 1;
     if (s.o.kb > s.o.chunks) s.o.kb = s.o.chunks;
+    if (two_planes)
+      for (uint32_t d = uint32_t(1.25 * 1024 * 1024 / (s.o.zb * row)); 3 * d >= 2 * s.o.kb && d > 0; --d)
+        if (s.o.chunks % d == 0) {
+          s.o.kb = d;
+          break;
+        }
   }
   // DSLASH_FLAT_ZB, DSLASH_FLAT_KB: from 1 to the whole range, which 0 and below stand
   // for too (flat_site divides by the products of these)

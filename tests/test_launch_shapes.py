@@ -288,3 +288,11 @@ def test_staggered_flat_takes_what_it_is_faster_at(shapes, dtype, dims, nv, comp
 ])
 def test_wilson_flat_takes_what_it_is_faster_at(shapes, dtype, dims, nv, clover, compressed, us, direct):
     assert bool(shapes.wilson_pays(dtype, _dims(dims), nv, clover, compressed)) == (us < direct)
+
+
+def test_flat_tiles_of_few_planes(shapes):
+    # FP64, N_v = 24 on 64 x 4 x 4 x 16: 61 us in tiles of 2 planes x 13 of 26 chunks, 84 in 3 x 7
+    s = _flat(shapes, (64, 4, 4, 16), 24, 12, 16, 1)
+    assert (s["zb"], s["kb"], s["chunks"]) == (2, 13, 26)
+    s = _flat(shapes, (24, 24, 24, 48), 12, 12, 16, 1)  # 1050 us, 3 planes x 7 of 28 chunks
+    assert (s["zb"], s["kb"], s["chunks"]) == (3, 7, 28)
