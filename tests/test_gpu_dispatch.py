@@ -3,7 +3,7 @@ only when a tuning variable asks for them, against the FP64 oracle."""
 import pytest
 
 import synthetic
-from oracle import compress, staggered, wilson
+from oracle import brillouin, compress, evenodd, staggered, wilson
 from tests.gpu_util import compare, down, rounded, say, set_knob, up
 
 pytestmark = pytest.mark.gpu
@@ -90,3 +90,76 @@ def test_columns_do_not_depend_on_the_block_size(dt, nx, monkeypatch):
                 sl[axis] = slice(c0, c0 + k)
                 part = D.apply("wilson", U, P[tuple(sl)].contiguous(), 0.1, adjoint=adj)
                 assert torch.equal(part, full[tuple(sl)]), (k, c0)
+
+
+# The row-staged kernels on compressed links, which lattices of a test's size take only
+# when asked (DSLASH_ROWS=2: those kernels or an error): D_W marches in chunks of one
+# x-row (16) and, asked for chunks of 13, across row ends; D_S in rows of 16 and 13 + 13
+@pytest.mark.parametrize("op,dt", [("wilson", "c64"), ("wilson", "bf16"), ("wilson", "f16"), ("staggered", "c64"),
+                                   ("staggered", "c128")])
+@pytest.mark.parametrize("dims", [(16, 4, 2, 8), (26, 2, 2, 4)])
+def test_compressed_links_by_rows(op, dt, dims, monkeypatch):
+    nv = 12
+    say(f"case compressed rows {op} {dims} {dt}")
+    vc = rounded(compress.compress(synthetic.gauge_links(dims, "smooth", 930)), dt)
+    gen = synthetic.wilson_spinor if op == "wilson" else synthetic.staggered_spinor
+    p = rounded(gen(dims, nv, 931), dt)
+    VC, P = up(vc, dt), up(p, dt)
+    set_knob(monkeypatch, "DSLASH_ROWS", "2")
+    for adj in (False, True):
+        ref = compress.apply(op, vc, p, 0.1, adj)
+        compare(down(D.apply_compressed(op, VC, P, 0.1, adjoint=adj)), ref, dt, f"{op} compressed adj={adj}")
+    if op == "wilson":
+        set_knob(monkeypatch, "DSLASH_ROW_SITES", "13")
+        compare(down(D.apply_compressed(op, VC, P, 0.1)), compress.apply(op, vc, p, 0.1, False), dt, "13 sites")
+
+
+# D_B on stored links by the kernel that stages the runs, required, and by the direct one
+@pytest.mark.parametrize("dims", [(16, 3, 2, 4), (12, 2, 3, 3), (24, 3, 2, 2)])
+def test_brillouin_staged_and_direct(dims, monkeypatch):
+    nv, dt = 12, "c64"
+    say(f"case brillouin staged and direct {dims}")
+    w = rounded(brillouin.build(synthetic.gauge_links(dims, "haar", 940)), dt)
+    p = rounded(synthetic.wilson_spinor(dims, nv, 941), dt)
+    W, P = up(w, dt), up(p, dt)
+    out = {}
+    for rows in ("2", "0"):
+        set_knob(monkeypatch, "DSLASH_ROWS", rows)
+        out[rows] = D.apply("brillouin", W, P, 0.1)
+        compare(down(out[rows]), brillouin.apply(w, p, 0.1, False), dt, f"D_B DSLASH_ROWS={rows}")
+    assert not torch.equal(out["2"], out["0"])
+
+
+# The even-odd hop by rows, required, against the direct one; packed rows of 27, 16 and 24
+@pytest.mark.parametrize("dims,nv", [((54, 2, 4, 2), 12), ((32, 4, 4, 4), 8), ((48, 4, 2, 2), 4)])
+def test_even_odd_hop_by_rows_and_direct(dims, nv, monkeypatch):
+    dt = "c64"
+    say(f"case even-odd rows and direct {dims} nv={nv}")
+    u = rounded(synthetic.gauge_links(dims, "haar", 950), dt)
+    p = rounded(synthetic.wilson_spinor(dims, nv, 951), dt)
+    Ue, Uo = up(evenodd.pack(u, 0), dt), up(evenodd.pack(u, 1), dt)
+    pe = evenodd.pack(p, 0)
+    out = {}
+    for rows in ("2", "0"):
+        set_knob(monkeypatch, "DSLASH_ROWS", rows)
+        out[rows] = D.eo_hop(Ue, Uo, up(pe, dt), 1)
+        compare(down(out[rows]), evenodd.hop_eo(u, pe, 1, False), dt, f"eo hop DSLASH_ROWS={rows}")
+    assert not torch.equal(out["2"], out["0"])
+
+
+# Spinors that begin one complex number past a 16-byte border: one column a lane
+@pytest.mark.parametrize("dt,op", [("c64", "wilson"), ("c64", "staggered"), ("bf16", "wilson"), ("f16", "staggered")])
+def test_fields_off_a_16_byte_border(dt, op, monkeypatch):
+    dims, nv = (6, 4, 2, 4), 12
+    say(f"case off a 16-byte border {op} {dt}")
+    set_knob(monkeypatch, "DSLASH_FLAT_LANES", "0")
+    u = rounded(synthetic.gauge_links(dims, "haar", 960), dt)
+    gen = synthetic.wilson_spinor if op == "wilson" else synthetic.staggered_spinor
+    p = rounded(gen(dims, nv, 961), dt)
+    U, P = up(u, dt), up(p, dt)
+    step = 1 if dt == "c64" else 2  # (16-bit fields hold pairs)
+    Q, out = (torch.zeros(P.numel() + step, dtype=P.dtype, device=P.device)[step:].view(P.shape) for _ in range(2))
+    Q.copy_(P)
+    assert Q.data_ptr() % 16 and out.data_ptr() % 16
+    ref = (wilson if op == "wilson" else staggered).apply(u, p, 0.1, False)
+    compare(down(D.apply(op, U, Q, 0.1, out=out)), ref, dt, f"{op} off a border")
