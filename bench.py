@@ -74,10 +74,14 @@ def site_bytes(op: str, nv: int, eb: int, compressed: bool = False) -> int:
     return eb * (links + 2 * comps * nv)
 
 
+# The headline's kernel, its launch rule and every header of theirs.
+KERNEL_SOURCES = ("dslash_common.hpp", "stencils.hpp", "rows.hpp", "tiles.hpp", "chunks.hpp", "launch.hpp", "apply.hip",
+                  "apply_rows.hip", "rows_shape.hpp", "wilson_rows.hpp", "wilson_rows_c64.hip")
+
+
 def kernel_source_hash() -> str:
     h = hashlib.sha256()
-    for f in ("dslash_common.hpp", "stencils.hpp", "rows.hpp", "tiles.hpp", "apply.hip", "apply_rows.hip",
-              "wilson_rows.hpp", "wilson_rows_c64.hip"):
+    for f in KERNEL_SOURCES:
         with open(os.path.join(ROOT, "paper_1808_05506_amd", "csrc", f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()[:16]

@@ -59,3 +59,15 @@ def test_stored_traffic_counts_only_for_its_sources(tmp_path, monkeypatch):
     monkeypatch.setattr(bench, "kernel_source_hash", lambda: "0" * 16)
     assert bench.measured_traffic("wilson_16^3x32_nv12_fp32") is None
     assert bench.measured_traffic("no such workload") is None
+
+
+def test_source_hash_covers_the_headers_of_the_kernel():
+    csrc = os.path.join(ROOT, "paper_1808_05506_amd", "csrc")
+    todo, seen = ["wilson_rows_c64.hip", "apply_rows.hip", "apply.hip"], set()
+    while todo:
+        f = todo.pop()
+        if f not in seen:
+            seen.add(f)
+            with open(os.path.join(csrc, f)) as fh:
+                todo += [ln.split('"')[1] for ln in fh if ln.startswith('#include "')]
+    assert seen <= set(bench.KERNEL_SOURCES)
