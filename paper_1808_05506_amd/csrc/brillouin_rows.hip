@@ -374,8 +374,8 @@ bool brillouin_rows_cover(int dtype, const Geom& g, bool clover) {
 }
 
 // D_B with the off-axis links built from V inside the row-staged kernel (no W
-// array).  The FP32 configurations of launch_brillouin_rows (N_v = 4, 8, 12,
-// 16, 24; the clover term at N_v = 12); hipErrorNotSupported otherwise.
+// array).  FP32 storage at N_v = 4, 8, 12, 16, 24 (the clover term at N_v = 12);
+// hipErrorNotSupported otherwise.
 hipError_t launch_brillouin_fly(bool adj, int dtype, const Geom& g, const void* V, const void* in, void* out,
                                 double mass, hipStream_t st, const void* clover) {
   if (!aligned16(V) || !aligned16(in) || !aligned16(out) || !aligned16(clover)) return hipErrorNotSupported;

@@ -6,7 +6,7 @@
 // of them L2 hits; the order of the tiles moves it by a few percent only.  So the
 // lanes stay filled (chunks across row ends, wide pieces), which is what the
 // row-staged kernel lacks where its chunks do not divide an x-row: N_v = 12,
-// 18x14x20x26 C64 42 us (69 before), 34^4 428 (488); 22x18x20x16 FP64 71 (80);
+// 18x14x20x26 C64 42 us (69 before), 34^4 406 (488); 22x18x20x16 FP64 71 (80);
 // 32^4 BF16 206 (269), FP16 200 (275); N_v = 7, 32^4 C64 269 (434), 22x18x20x16
 // FP64 54 (107).  Where they do, 32^4 C64 takes 284 us by rows, 300 here.
 #include "flat_rule.hpp"

@@ -582,7 +582,7 @@ static hipError_t staggered_march_nv(bool adj, int dtype, const Geom& g, int R, 
 
 // Row-staged D_S in C64 and C128 for N_v = 4, 8, 12, 16, 24.  Returns
 // hipErrorNotSupported when the configuration is not covered (the caller then
-// uses the direct kernel).  DSLASH_ROWS=0 disables it.
+// uses the flat or the direct kernel).  DSLASH_ROWS=0 disables it.
 hipError_t launch_staggered_rows(bool adj, int dtype, const Geom& g, const void* U, const void* in, void* out,
                                  double mass, hipStream_t st, bool compressed) {
   if (knobs().rows.get(1) == 0) return hipErrorNotSupported;
@@ -600,7 +600,7 @@ hipError_t launch_staggered_rows(bool adj, int dtype, const Geom& g, const void*
   if (R < 6 || R * nv > 256 || R * nv < 64) return hipErrorNotSupported;
   // rows that leave few lanes idle; the others are faster in flat order (N_v = 12,
   // C64: 24^3 x 48, 75 % of the lanes, 208 us against 195; 34^4, 71 %, 488 against
-  // 403; 32^4, all, 284 against 300.  N_v = 4, 8, where a site's runs are short:
+  // 406; 32^4, all, 284 against 300.  N_v = 4, 8, where a site's runs are short:
   // 28^4, N_v = 8, 88 %, 132 against 142; 20^4, N_v = 4 FP64, 63 %, 45 against 51)
   const bool asked = knobs().rows.get(1) == 2 || knobs().row_sites.set || knobs().row_depth.set || knobs().tsteps.set;
   // and lattices that fill the chip with marching workgroups: below that the rows

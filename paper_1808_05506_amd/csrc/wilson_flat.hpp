@@ -141,9 +141,9 @@ __device__ __forceinline__ void flat_half(const typename FlatVec<S, VW>::V (&raw
     }
 }
 
-// Half hops in flight and waves per SIMD: three at one column a lane in FP32
-// arithmetic (74 VGPRs, 6 waves), two at more columns (two: 128 VGPRs, 4 waves) and
-// for FP64 (114, 4 waves).
+// Half hops in flight, and the waves per SIMD whose registers they fit in: three at one
+// column a lane in FP32 arithmetic (69 to 85 VGPRs), two elsewhere (C64, two columns, 128,
+// 135 with the clover term; FP64 112 to 136; four columns of 16 bits 179 to 238).
 template <class S, int VW>
 struct FlatDepth {
   static constexpr int LANE = VW * int(sizeof(typename S::real));
