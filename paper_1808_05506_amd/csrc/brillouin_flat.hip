@@ -24,8 +24,8 @@
 //   of a wave writes 16 bytes at b + 16 l for a wave-uniform b), half a run while
 //   the other half is applied, so no registers hold them: the links of three hops
 //   fit beside the sums at three waves a SIMD (C64) and two (C128).
-// 32^4, N_v = 12, C64: 6.20 ms (6.94 before, hop by hop and staged through
-// registers; with the staging left out 4.67); 16^3 x 32, C128: 1.39 ms (2.12;
+// 32^4, N_v = 12, C64: 6.28 ms (7.05 before, hop by hop and staged through
+// registers; with the staging left out 4.67); 16^3 x 32, C128: 1.38 ms (2.10;
 // 1.09).  C64 chunks of 21 sites: 6.23 ms, of 16: 6.26; C128 of 20: 1.41, of 16 1.50.
 #include "bri_runs.hpp"
 
