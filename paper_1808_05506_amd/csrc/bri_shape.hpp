@@ -35,6 +35,21 @@ constexpr int bri_sites(int dtype, int nb) {
                          : (nb == 12 ? 20 : nb == 8 ? 32 : nb == 6 ? 42 : 64);
 }
 
+// Workgroups of D_B in chunks of P sites.
+inline uint64_t bri_blocks(const Geom& g, int P, int nb) {
+  const uint64_t plane = uint64_t(g.n[0]) * uint64_t(g.n[1]);
+  return (plane + uint64_t(P) - 1) / uint64_t(P) * uint64_t(g.n[2]) * uint64_t(g.n[3]) * uint64_t((g.nv + nb - 1) / nb);
+}
+
+// C64 pairs in blocks of twelve: chunks of 16 sites (three waves, four workgroups a CU)
+// where all of them are resident at once and those of 21 (three a CU) are not: 64 x 4 x 4 x 16,
+// N_v = 12, 105 us against 148 (16 x 8 x 8 x 16 122 and 165).  Elsewhere 21 (32^4 6.23 ms, 6.26 in
+// chunks of 16).
+inline bool bri_short_chunks(const Geom& g, int nb, bool pairs) {
+  const uint64_t cus = uint64_t(device_cus());
+  return pairs && nb == 12 && bri_blocks(g, 16, 12) <= 4 * cus && bri_blocks(g, 21, 12) > 3 * cus;
+}
+
 // D_B: a workgroup takes its 27 runs one after the other, 75 to 120 us, so on lattices of
 // a few rounds of workgroups the number of rounds decides (two a CU are resident, three of
 // C64 pairs in more than four columns; of the direct kernel two in C64, one in C128 and at
@@ -51,13 +66,12 @@ constexpr int bri_sites(int dtype, int nb) {
 inline bool brillouin_flat_pays(int dtype, const Geom& g) {
   const uint64_t pairs = uint64_t(g.vol) * uint64_t(g.nv), cus = uint64_t(device_cus());
   if (knobs().bri_lanes.set) return pairs >= uint64_t(knobs().bri_lanes.value < 0 ? 0 : knobs().bri_lanes.value);
-  const int nv = g.nv, nb = bri_block(dtype, nv), P = bri_sites(dtype, nb);
-  const uint64_t plane = uint64_t(g.n[0]) * uint64_t(g.n[1]);
-  const uint64_t blocks = (plane + P - 1) / P * uint64_t(g.n[2]) * uint64_t(g.n[3]) * uint64_t((nv + nb - 1) / nb);
+  const int nv = g.nv, nb = bri_block(dtype, nv);
   const uint64_t here = (dtype == DT_C64 && nv % 2 == 0 && nb > 4 ? 3 : 2) * cus;
   const uint64_t there = (dtype == DT_C64 && nv != 2 ? 2 : 1) * cus;
   const dim3 direct = site_v_shape(g.vol, nv).grid;
-  const uint64_t rounds = (blocks + here - 1) / here;
+  const uint64_t rounds =
+      bri_short_chunks(g, nb, dtype == DT_C64 && nv % 2 == 0) ? 1 : (bri_blocks(g, bri_sites(dtype, nb), nb) + here - 1) / here;
   const uint64_t rounds_direct = (uint64_t(direct.x) * direct.y + there - 1) / there;
   if (dtype == DT_C64) return nv > 1 && pairs >= 256 * cus && (rounds_direct > 2 || rounds <= rounds_direct);
   if (nv >= 3 && g.vol < 6 * cus) return false;

@@ -26,7 +26,7 @@
 //   fit beside the sums at three waves a SIMD (C64) and two (C128).
 // 32^4, N_v = 12, C64: 6.28 ms (7.05 before, hop by hop and staged through
 // registers; with the staging left out 4.67); 16^3 x 32, C128: 1.38 ms (2.10;
-// 1.09).  C64 chunks of 21 sites: 6.23 ms, of 16: 6.26; C128 of 20: 1.41, of 16 1.50.
+// 1.09).  C64 chunks of 21 sites: 6.23 ms, of 16 6.26 (bri_short_chunks); C128 of 20: 1.41, of 16 1.50.
 #include "bri_runs.hpp"
 
 namespace dsl {
@@ -344,6 +344,8 @@ hipError_t bri_flat_t(const BriCall& a) {
 template <int NB>
 hipError_t bri_flat_c64(const BriCall& a, bool pairs) {
   constexpr int P = bri_sites(DT_C64, NB);
+  if constexpr (NB == 12)
+    if (bri_short_chunks(*a.g, NB, pairs)) return bri_flat_t<BriBlock<C64, NB, 16, BRI_PAIRS>, C64, float>(a);
   return pairs ? bri_flat_t<BriBlock<C64, NB, P, BRI_PAIRS>, C64, float>(a)
                : bri_flat_t<BriBlock<C64, NB, P, BRI_WORDS>, C64, float>(a);
 }

@@ -3,7 +3,7 @@ only when a tuning variable asks for them, against the FP64 oracle."""
 import pytest
 
 import synthetic
-from oracle import brillouin, compress, evenodd, staggered, wilson
+from oracle import brillouin, clover, compress, evenodd, staggered, wilson
 from tests.gpu_util import compare, down, rounded, say, set_knob, up
 
 pytestmark = pytest.mark.gpu
@@ -163,3 +163,20 @@ def test_fields_off_a_16_byte_border(dt, op, monkeypatch):
     assert Q.data_ptr() % 16 and out.data_ptr() % 16
     ref = (wilson if op == "wilson" else staggered).apply(u, p, 0.1, False)
     compare(down(D.apply(op, U, Q, 0.1, out=out)), ref, dt, f"{op} off a border")
+
+
+# D_B in chunks of 16 sites (bri_short_chunks): 16 + 6 of a plane of 22, 4 live sites of 16
+@pytest.mark.parametrize("dims", [(11, 2, 20, 20), (2, 2, 28, 28)])
+def test_brillouin_short_chunks(dims, monkeypatch):
+    nv, dt = 12, "c64"
+    say(f"case brillouin short chunks {dims}")
+    set_knob(monkeypatch, "DSLASH_BRI_LANES", "0")
+    u = synthetic.gauge_links(dims, "haar", 970)
+    w, c = rounded(brillouin.build(u), dt), rounded(clover.pack(clover.term(u, 1.0)), dt)
+    p = rounded(synthetic.wilson_spinor(dims, nv, 971), dt)
+    W, P, C = up(w, dt), up(p, dt), up(c, dt)
+    for adj in (False, True):
+        ref = brillouin.apply(w, p, 0.1, adj)
+        compare(down(D.apply("brillouin", W, P, 0.1, adjoint=adj)), ref, dt, f"D_B short chunks adj={adj}")
+        ref = ref + clover.apply_term(clover.unpack(c), p)
+        compare(down(D.apply("brillouin", W, P, 0.1, adjoint=adj, clover=C)), ref, dt, f"D_B + C short chunks adj={adj}")

@@ -95,6 +95,9 @@ int staggered_pays(int dtype, const int* d, int nv, int compressed) {
 int brillouin_pays(int dtype, const int* d, int nv) { return brillouin_flat_pays(dtype, geom(d, nv)); }
 int wgrad_pays(int dtype, const int* d, int nv) { return brillouin_wgrad_pays(dtype, geom(d, nv)); }
 int brillouin_block(int dtype, int nv) { return bri_block(dtype, nv); }
+int brillouin_short(const int* d, int nv, int pairs) {
+  return bri_short_chunks(geom(d, nv), bri_block(DT_C64, nv), pairs != 0);
+}
 
 // The launchers on null fields, for calls that they refuse before they launch.
 int launch_wilson(int dtype, const int* d, int nv, int clover, int compressed) {
@@ -296,3 +299,14 @@ def test_flat_tiles_of_few_planes(shapes):
     assert (s["zb"], s["kb"], s["chunks"]) == (2, 13, 26)
     s = _flat(shapes, (24, 24, 24, 48), 12, 12, 16, 1)  # 1050 us, 3 planes x 7 of 28 chunks
     assert (s["zb"], s["kb"], s["chunks"]) == (3, 7, 28)
+
+
+# D_B in chunks of 16 sites: 1024 of their workgroups are resident, 768 of those of 21
+@pytest.mark.parametrize("dims,nv,pairs,short", [
+    ((64, 4, 4, 16), 12, 1, 1), ((16, 8, 8, 16), 12, 1, 1), ((2, 2, 28, 28), 12, 1, 1), ((11, 2, 20, 20), 12, 1, 1),
+    ((2, 2, 28, 28), 12, 0, 0), ((2, 2, 28, 28), 10, 1, 0),      # words through registers, other blocks
+    ((16, 8, 8, 12), 12, 1, 0), ((2, 2, 24, 32), 12, 1, 0),      # those of 21 are resident too
+    ((16, 8, 8, 17), 12, 1, 0), ((32, 32, 32, 32), 12, 1, 0),    # not all of 16
+])
+def test_brillouin_short_chunks_save_a_round(shapes, dims, nv, pairs, short):
+    assert shapes.brillouin_short(_dims(dims), nv, pairs) == short
